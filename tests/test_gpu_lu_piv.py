@@ -154,3 +154,48 @@ def test_full_size_n16384_properties(torch, T):
           flush=True)
     assert rel <= 8 * n * U64
     assert berr <= 8 * n * U64
+
+
+@pytest.mark.parametrize("n,nb,pad", [(1023, 256, 0), (1024, 256, 1), (1025, 256, 2),
+                                      (1056, 64, 3), (2049, 32, 0)])
+def test_panel_workgroup_edges_match_the_oracle(torch, T, n, nb, pad):
+    # panels of up to 1024 rows are one workgroup, taller ones meet per column;
+    # rows 16-byte aligned or not (leading dimension even or odd), ragged last
+    # panels, exchanges that reach into other workgroups' rows
+    A = gen.rng(900 + n).standard_normal((n, n))
+    A[::3] *= 2.0 ** -6          # most pivots come from far rows
+    buf = torch.full((n, n + pad), float("nan"), dtype=torch.float64, device="cuda")
+    buf[:, :n] = torch.from_numpy(A).cuda()
+    f = T.LUPiv(n, nb)
+    f.factor(buf[:, :n])
+    st, idx = f.check()
+    Lo, Uo, po, fail = oracle.lu_piv(A)
+    F = buf[:, :n].cpu().numpy()
+    assert st == T.OK and idx == -1 and fail == -1
+    assert np.array_equal(f.ipiv.cpu().numpy(), po)
+    # the same tolerance as the oracle comparison at these sizes above
+    assert np.abs(np.tril(F, -1) - np.tril(Lo, -1)).max() <= 1e-11
+    assert np.abs(np.triu(F) - Uo).max() <= 1e-11 * np.abs(Uo).max()
+    assert bool(torch.isnan(buf[:, n:]).all())
+
+
+@pytest.mark.parametrize("n,k,k0,k1", [(5, 1, 0, 5), (40, 3, 3, 40), (100, 300, 0, 100),
+                                       (97, 7, 31, 64)])
+def test_row_swaps_any_order(torch, T, n, k, k0, k1):
+    # exchanges with rows above, inside and below each group of 32, repeated
+    # targets and no-ops, in a matrix with padded rows: the same bits as one
+    # exchange at a time
+    g = gen.rng(n + k)
+    ip = g.integers(0, n, size=n)
+    ip[::4] = n - 1
+    ip[1::5] = np.arange(n)[1::5]
+    B = g.standard_normal((n, k))
+    buf = torch.full((n, k + 5), float("nan"), dtype=torch.float64, device="cuda")
+    buf[:, :k] = torch.from_numpy(B).cuda()
+    ipd = torch.from_numpy(ip).cuda()
+    T.trsm_row_swaps(k0, k1, ipd.data_ptr(), buf.data_ptr(), k + 5, k,
+                     torch.cuda.current_stream().cuda_stream)
+    for i in range(k0, k1):
+        B[[i, ip[i]]] = B[[ip[i], i]]
+    assert np.array_equal(buf[:, :k].cpu().numpy(), B)
+    assert bool(torch.isnan(buf[:, k:]).all())
