@@ -18,9 +18,9 @@
 //     U(S_j, T_j) = Linv_jj A(S_j, T_j)         (the panel solve: one product)
 //     A(T_j, T_j) -= L(T_j, S_j) U(S_j, T_j)
 //
-// The panel kernel keeps the panel in registers (kRpt rows per thread, kRows
-// rows per workgroup).  A panel of at most kRows rows is one workgroup and
-// needs no device-wide meeting; taller ones run on G co-resident workgroups
+// The panel kernel keeps the panel in registers (one or two rows per thread).
+// A panel of at most 1024 rows is one workgroup and needs no device-wide
+// meeting; taller ones run on G co-resident workgroups
 // (cooperative launch) that meet once per column: every workgroup publishes
 // its best candidate (largest magnitude, the first position on ties, positions
 // being the row order after the exchanges so far) together with that row's
@@ -47,12 +47,11 @@ constexpr int kPw = 32;               // panel width
 constexpr int kSub = 8;               // columns per unrolled group of steps
 constexpr int kThreads = 512;         // threads per panel workgroup
 constexpr int kWaves = kThreads / 64;
-constexpr int kRpt = 2;               // panel rows per thread
-constexpr int kRows = kThreads * kRpt;   // panel rows per workgroup
+constexpr int kMaxRpt = 2;            // panel rows per thread: 1 or 2
 constexpr int64_t kMaxN = 65536;      // rows a panel may have (positions fit a slot's tags)
-constexpr int kMaxGroups = (int)(kMaxN / kRows);   // workgroups of a panel
+constexpr int kMaxGroups = (int)(kMaxN / (kThreads * kMaxRpt));   // workgroups of a panel
 constexpr int kSlotWords = 2 * kPw;   // 8-byte words of a candidate slot
-constexpr int kNoPos = (1 << 30) - 1; // position of "no candidate"
+constexpr int kNoPos = (1 << 20) - 1; // position of "no candidate" (times kWaves fits an int)
 constexpr unsigned kSpinLimit = 1u << 22;
 constexpr size_t kAl = 256;
 constexpr size_t kSplitBytes = (size_t)32 << 20;
@@ -73,71 +72,78 @@ struct Moves {
   int dst[kPw];
 };
 
-__device__ __forceinline__ bool better(double a, int pa, double b, int pb) {
-  // larger magnitude first; on equal magnitudes the smaller position
-  return a > b || (a == b && pa < pb);
+// Rank of a row in the pivot search, as an integer so that the largest
+// magnitude is the largest rank: 0 for no row, 1 for a NaN, else the bits of
+// |x| (which order like the values) plus 2.
+__device__ __forceinline__ unsigned long long pivot_rank(double x) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, x) & ~(1ull << 63);
+  return x == x ? b + 2 : 1;
 }
 
-// Rank of a row in the pivot search: its magnitude, NaN below every number.
-__device__ __forceinline__ double pivot_key(double x) {
-  x = fabs(x);
-  return x >= 0.0 ? x : -0.5;
-}
+// A candidate for the pivot: its rank and position.
+struct __attribute__((aligned(16))) Cand {
+  unsigned hi, lo;   // the rank
+  int pos, unused;
+};
 
-template <int CTRL>
-__device__ __forceinline__ double dpp_max(double v) {
+// Lane `lane`'s v (a wave-uniform lane), in scalar registers.
+__device__ __forceinline__ double lane_value(double v, int lane) {
   const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-  const int lo = (int)(unsigned)b, hi = (int)(unsigned)(b >> 32);
-  const unsigned l2 = (unsigned)__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xF, 0xF, false);
-  const unsigned h2 = (unsigned)__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xF, 0xF, false);
-  return fmax(v, __builtin_bit_cast(double, ((unsigned long long)h2 << 32) | l2));
-}
-
-// Largest v of the wave (no NaN), in every lane: row shifts by 1, 2, 4, 8,
-// then the two row broadcasts; lane 63 holds the maximum.
-__device__ __forceinline__ double wave_max(double v) {
-  v = dpp_max<0x111>(v);
-  v = dpp_max<0x112>(v);
-  v = dpp_max<0x114>(v);
-  v = dpp_max<0x118>(v);
-  v = dpp_max<0x142>(v);
-  v = dpp_max<0x143>(v);
-  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, 63);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), 63);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, lane);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), lane);
   return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
-// The best of kWaves candidates (largest value, smallest position on ties):
-// its value, position and index, all wave-uniform.
-__device__ __forceinline__ void pick(const double* v, const int* p, double& best, int& bp, int& bi) {
-  double m = v[0];
-#pragma unroll
-  for (int i = 1; i < kWaves; ++i) m = fmax(m, v[i]);
-  int mp = INT32_MAX, mi = 0;
-#pragma unroll
-  for (int i = 0; i < kWaves; ++i) {
-    const int pi = v[i] == m ? p[i] : INT32_MAX;
-    if (pi < mp) {
-      mp = pi;
-      mi = i;
-    }
+template <int CTRL>
+__device__ __forceinline__ unsigned dpp_max(unsigned v) {
+  return max(v, (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xF, 0xF, false));
+}
+
+// Largest v over lanes 0 .. LANES-1 (8 or 64), wave-uniform: row shifts by 1,
+// 2, 4 (lane 7 then holds lanes 0-7's), 8 and the two row broadcasts.
+template <int LANES>
+__device__ __forceinline__ unsigned lanes_max(unsigned v) {
+  v = dpp_max<0x111>(v);
+  v = dpp_max<0x112>(v);
+  v = dpp_max<0x114>(v);
+  if (LANES == 64) {
+    v = dpp_max<0x118>(v);
+    v = dpp_max<0x142>(v);
+    v = dpp_max<0x143>(v);
   }
-  best = m;
-  bp = __builtin_amdgcn_readfirstlane(mp);
-  bi = __builtin_amdgcn_readfirstlane(mi);
+  return (unsigned)__builtin_amdgcn_readlane((int)v, LANES - 1);
+}
+
+// The lane (of 0 .. LANES-1) with the best candidate: the largest rank, the
+// smallest position on ties.  One pass over the high words decides unless
+// several lanes share the largest one.
+template <int LANES>
+__device__ __forceinline__ int best_lane(const Cand& c) {
+  const unsigned long long in = LANES == 64 ? ~0ull : (1ull << LANES) - 1;
+  const unsigned mh = lanes_max<LANES>(c.hi);
+  unsigned long long mask = __ballot(c.hi == mh) & in;
+  if (mask & (mask - 1)) {
+    const unsigned ml = lanes_max<LANES>(c.hi == mh ? c.lo : 0u);
+    const bool top = c.hi == mh && c.lo == ml;
+    const unsigned mp = lanes_max<LANES>(top ? ~(unsigned)c.pos : 0u);
+    mask = __ballot(top && ~(unsigned)c.pos == mp) & in;
+  }
+  return __ffsll(mask) - 1;
 }
 
 // Panel A(r0:r0+h, c0:c0+w) (w <= kPw) factored with row exchanges by G =
-// gridDim.x co-resident workgroups (MULTI) or by one; workgroup g owns rows
-// g*kRows.. of the panel, thread t of it rows t, t + kThreads, ...  ipiv[c0 +
-// j] receives the absolute row exchanged with row r0 + j, *mv the panel's net
-// row moves.
+// gridDim.x co-resident workgroups (MULTI) or by one; workgroup g owns
+// kThreads RPT rows of the panel, thread t of it rows t, t + kThreads, ...
+// ipiv[c0 + j] receives the absolute row exchanged with row r0 + j, *mv the
+// panel's net row moves.
 //
 // What bounds it is the chain of w steps, each a search over the whole column
 // that needs the previous step's update, so the step is kept short:
-//  * search: a wave reduces its column by DPP; its best lane puts its row into
-//    LDS, and after the one barrier every wave picks the workgroup's best;
+//  * search: a wave reduces its column's ranks by DPP and shows its best; after
+//    a barrier every wave picks the workgroup's best from the kWaves shown, and
+//    only that row goes through LDS, its columns from j on (a 16-byte LDS write
+//    of one lane costs about 16 cycles of the unit's LDS, so eight waves
+//    showing whole rows took longer than the second barrier);
 //  * meeting (MULTI): the winner's wave stores the row as 64 words of
 //    {32 bits of data, step << 15 | 15 bits of the position}; 8-byte words
 //    arrive whole, so a reader that sees the step number in a word has its
@@ -145,38 +151,38 @@ __device__ __forceinline__ void pick(const double* v, const int* p, double& best
 //    v + kWaves, ...; two slots per workgroup, by step parity, suffice: a
 //    workgroup publishes step j + 1 only after it has seen everyone's step j,
 //    and everyone publishes step j after reading all of step j - 1;
-//  * update: the columns right of j by the winner's row from LDS.
+//  * update: the columns right of j; every lane reads one element of the pivot
+//    row and the rest comes by readlane (LDS broadcasts of the row to eight
+//    waves cost more).  Not masked: a pivot row's U part is written back at its
+//    step, and its L part, the columns before, is no longer touched.
 // Steps are unrolled in groups of kSub so that registers are indexed
-// statically; after a group the columns move down by kSub places (cyclically:
-// after kPw / kSub groups they are back), and columns that already hold L are
-// left out of the update.
-// Measured: 3.5 us per column on two to four workgroups (panels of 1025 to
-// 4096 rows, of which about 0.4 us is the panel's load and store), 2.0 us on
-// one; 11 to 16 us with one device-wide arrival counter and fences a column
-// and 256 rows a workgroup.
-template <bool MULTI>
+// statically (4 and 2 measured the same to 4 % slower); after a group the
+// columns move down by kSub places (cyclically: after kPw / kSub groups they
+// are back), and columns that already hold L are left out of the update.
+// Measured per column: about 1.1 us on one workgroup, 2.4 us on several (1.3
+// of it the store and load of the candidates); 11 to 16 us with one
+// device-wide arrival counter and fences a column and 256 rows a workgroup.
+template <int RPT, bool MULTI>
 __global__ __launch_bounds__(kThreads) void piv_panel_kernel(
     double* __restrict__ A, int64_t lda, int64_t r0, int64_t c0, int h, int w,
     int64_t* __restrict__ ipiv, unsigned long long* __restrict__ slots, Words* __restrict__ words,
     Moves* __restrict__ mv) {
   typedef double D2 __attribute__((ext_vector_type(2)));
-  __shared__ __attribute__((aligned(16))) double wrow[2][kWaves][kPw];   // a wave's best row
-  __shared__ double wv[2][kWaves];
-  __shared__ int wp[2][kWaves];
+  __shared__ __attribute__((aligned(16))) double row[2][kPw];   // the workgroup's best row
+  __shared__ Cand wcand[2][kWaves];
   __shared__ __attribute__((aligned(16))) double grow[MULTI ? 2 : 1][kWaves][kPw];
-  __shared__ double gv[2][kWaves];
-  __shared__ int gp[2][kWaves];
+  __shared__ Cand gcand[2][kWaves];
   __shared__ int piv[kPw];
   const int G = MULTI ? (int)gridDim.x : 1, g = blockIdx.x, tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  double a[kRpt][kPw];
-  int pos[kRpt];                          // position in the exchanged order
-  bool act[kRpt];
+  double a[RPT][kPw];
+  int pos[RPT];                           // position in the exchanged order
+  bool act[RPT];
   const bool vec = (lda & 1) == 0 && w == kPw;   // rows 16-byte aligned (c0 is even)
 #pragma unroll
-  for (int r = 0; r < kRpt; ++r) {
-    const int lr = g * kRows + r * kThreads + tid;   // panel row (original order)
+  for (int r = 0; r < RPT; ++r) {
+    const int lr = g * (kThreads * RPT) + r * kThreads + tid;   // panel row (original order)
     pos[r] = lr;
     act[r] = lr < h;
     const double* src = A + (r0 + (act[r] ? lr : 0)) * lda + c0;
@@ -192,6 +198,39 @@ __global__ __launch_bounds__(kThreads) void piv_panel_kernel(
       for (int c = 0; c < kPw; ++c) a[r][c] = c < w ? src[c] : 0.0;
     }
   }
+  // every row has arrived before anyone may write the panel back: the empty asm
+  // uses the registers, so the loads are waited for here
+#pragma unroll
+  for (int r = 0; r < RPT; ++r)
+#pragma unroll
+    for (int c = 0; c < kPw; ++c) asm volatile("" : "+v"(a[r][c]));
+  // the next step's candidate: the lane's best row, then the wave's best lane
+  Cand mine;
+  int rv, wl;
+  auto search = [&](const double (&x)[RPT]) {
+    unsigned long long k = act[0] ? pivot_rank(x[0]) : 0;
+    int pk = act[0] ? pos[0] : kNoPos;
+    rv = 0;
+#pragma unroll
+    for (int r = 1; r < RPT; ++r) {
+      const unsigned long long kr = act[r] ? pivot_rank(x[r]) : 0;
+      const int pr = act[r] ? pos[r] : kNoPos;
+      const bool better = kr > k || (kr == k && pr < pk);
+      k = better ? kr : k;
+      pk = better ? pr : pk;
+      rv = better ? r : rv;
+    }
+    mine.hi = (unsigned)(k >> 32);
+    mine.lo = (unsigned)k;
+    mine.pos = pk;
+    wl = best_lane<64>(mine);
+  };
+  {
+    double x[RPT];
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) x[r] = a[r][0];
+    search(x);
+  }
   bool dead = false;                      // a wait gave up: later ones do not wait
   for (int q = 0; q < kPw / kSub; ++q) {
 #pragma unroll
@@ -199,48 +238,39 @@ __global__ __launch_bounds__(kThreads) void piv_panel_kernel(
       const int j = q * kSub + jj;
       if (j < w) {
         const int par = jj & 1;           // kSub is even: the parity of j
-        // the wave's candidate
-        double v = -1.0;
-        int pv = kNoPos, rv = 0;
+        if (lane == wl) wcand[par][wave] = mine;
+        __syncthreads();
+        // the workgroup's candidate; its thread shows the row's columns from j
+        // on (columns before j, already L, stay in its registers)
+        Cand k = wcand[par][lane & (kWaves - 1)];
+        int sw = best_lane<kWaves>(k);
+        unsigned bhi = (unsigned)__builtin_amdgcn_readlane((int)k.hi, sw);
+        unsigned blo = (unsigned)__builtin_amdgcn_readlane((int)k.lo, sw);
+        int p = __builtin_amdgcn_readlane(k.pos, sw);
+        if (wave == sw && lane == wl) {
 #pragma unroll
-        for (int r = 0; r < kRpt; ++r) {
-          const double key = act[r] ? pivot_key(a[r][jj]) : -1.0;
-          if (act[r] && better(key, pos[r], v, pv)) {
-            v = key;
-            pv = pos[r];
-            rv = r;
-          }
-        }
-        const double m = wave_max(v);
-        unsigned long long mask = __ballot(v == m);
-        if (__popcll(mask) > 1) {         // ties: the smallest position
-          int pm = v == m ? pv : kNoPos;
+          for (int r = 0; r < RPT; ++r)
+            if (RPT == 1 || rv == r) {
+              auto show = [&](int cb, int ce) {
 #pragma unroll
-          for (int o = 32; o > 0; o >>= 1) pm = min(pm, __shfl_xor(pm, o, 64));
-          const unsigned long long first = __ballot(v == m && pv == pm);
-          if (first) mask = first;
-        }
-        if (lane == __ffsll(mask) - 1) {
-          wv[par][wave] = v;
-          wp[par][wave] = pv;
+                for (int c = cb; c < ce; c += 2)
+                  *reinterpret_cast<D2*>(&row[par][c]) = D2{a[r][c], a[r][c + 1]};
+              };
+              show(jj & ~1, kSub);
 #pragma unroll
-          for (int r = 0; r < kRpt; ++r)
-            if (rv == r) {
-#pragma unroll
-              for (int c = 0; c < kPw; c += 2)
-                *reinterpret_cast<D2*>(&wrow[par][wave][c]) = D2{a[r][c], a[r][c + 1]};
+              for (int b = 1; b < kPw / kSub; ++b)
+                if (q + b < kPw / kSub) show(b * kSub, (b + 1) * kSub);
             }
         }
-        __syncthreads();
-        // the workgroup's candidate
-        double best;
-        int p, sw;
-        pick(wv[par], wp[par], best, p, sw);
-        const double* u = wrow[par][sw];
+        double u;                         // the pivot row, column `lane` of this group's order
+        if constexpr (!MULTI) {
+          __syncthreads();
+          u = row[par][lane & (kPw - 1)];
+        }
         if constexpr (MULTI) {
           const unsigned step = (unsigned)(c0 + j + 1);
           if (wave == sw) {
-            const unsigned data = reinterpret_cast<const unsigned*>(&wrow[par][sw][0])[lane];
+            const unsigned data = reinterpret_cast<const unsigned*>(&row[par][0])[lane];
             const unsigned part = lane == 0 ? (unsigned)p & 0x7FFFu
                                             : lane == 1 ? (unsigned)p >> 15 : 0u;
             const unsigned long long word =
@@ -248,7 +278,7 @@ __global__ __launch_bounds__(kThreads) void piv_panel_kernel(
             __hip_atomic_store(&slots[((size_t)par * G + g) * kSlotWords + lane], word,
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           }
-          double cv = -1.0;
+          unsigned long long ck = 0;      // this wave's best candidate
           int cp = kNoPos;
           for (int c = wave; c < G; c += kWaves) {
             const unsigned long long* sl = slots + ((size_t)par * G + c) * kSlotWords + lane;
@@ -268,68 +298,82 @@ __global__ __launch_bounds__(kThreads) void piv_panel_kernel(
             const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)data, 2 * jj);
             const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)data, 2 * jj + 1);
             const double x = __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-            const double key = pc == kNoPos ? -1.0 : pivot_key(x);
-            if (better(key, pc, cv, cp)) {
-              cv = key;
+            const unsigned long long key = pc == kNoPos ? 0 : pivot_rank(x);
+            if (key > ck || (key == ck && pc < cp)) {
+              ck = key;
               cp = pc;
               reinterpret_cast<unsigned*>(&grow[par][wave][0])[lane] = data;
             }
           }
-          if (lane == 0) {
-            gv[par][wave] = cv;
-            gp[par][wave] = cp;
-          }
+          if (lane == 0) gcand[par][wave] = Cand{(unsigned)(ck >> 32), (unsigned)ck, cp, 0};
           __syncthreads();
-          pick(gv[par], gp[par], best, p, sw);
-          u = grow[par][sw];
+          k = gcand[par][lane & (kWaves - 1)];
+          sw = best_lane<kWaves>(k);
+          bhi = (unsigned)__builtin_amdgcn_readlane((int)k.hi, sw);
+          blo = (unsigned)__builtin_amdgcn_readlane((int)k.lo, sw);
+          p = __builtin_amdgcn_readlane(k.pos, sw);
+          u = grow[par][sw][lane & (kPw - 1)];
+          // a position outside j .. h-1 can only come from candidates read
+          // after a wait gave up (reported through the error word): fall back
+          // to j so that every row still goes back to a row of the panel
+          if (p < j || p >= h) {
+            p = j;
+            if (tid == 0) atomicOr(&words->err, 2u);
+          }
         }
-        // a position outside j .. h-1 can only come from candidates read after
-        // a wait gave up (reported through the error word): fall back to j so
-        // that every row still goes back to a row of the panel
-        if (p < j || p >= h) {
-          p = j;
-          if (tid == 0) atomicOr(&words->err, 2u);
-        }
+        const unsigned long long rank = (unsigned long long)bhi << 32 | blo;
+        // a zero, infinite or NaN pivot: ranks 2, of infinity, and below 2
+        const bool zero = rank <= 2 || rank - 2 >= 0x7FF0000000000000ull;
         if (tid == 0) piv[j] = p;
-        const bool zero = !(best > 0.0) || !(best <= 1.7976931348623157e308);
         if (zero && g == 0 && tid == 0) atomicMin(&words->bad, (unsigned long long)(c0 + j));
-        // exchange positions j and p; the pivot row leaves the elimination
+        // exchange positions j and p; the pivot row leaves the elimination and
+        // its U part is written back now (every workgroup has read its rows of
+        // the panel: it published a candidate from them): what its thread's
+        // registers of these columns hold afterwards no longer matters
+        if (g == 0 && wave == kWaves - 1 && lane < kPw) {
+          const int c = (lane + q * kSub) % kPw;
+          if (c >= j && c < w) A[(r0 + j) * lda + c0 + c] = u;
+        }
 #pragma unroll
-        for (int r = 0; r < kRpt; ++r) {
+        for (int r = 0; r < RPT; ++r) {
           if (act[r] && pos[r] == p) {
-            pos[r] = j;
             act[r] = false;
-          } else if (act[r] && pos[r] == j) {
-            pos[r] = p;
+            pos[r] = j;
+            const int lr = g * (kThreads * RPT) + r * kThreads + tid;
+            mv->src[j] = lr;
+            if (lr < w) mv->dst[lr] = j;
           }
+          if (act[r] && pos[r] == j) pos[r] = p;
         }
+        double x[RPT];
         if (!zero) {
-          double uc[kPw];
+          double l[RPT];
+          const double pj = lane_value(u, jj);
 #pragma unroll
-          for (int c = 0; c < kPw; c += 2) {
-            const D2 v2 = *reinterpret_cast<const D2*>(u + c);
-            uc[c] = v2.x;
-            uc[c + 1] = v2.y;
+          for (int r = 0; r < RPT; ++r) {
+            l[r] = a[r][jj] / pj;
+            a[r][jj] = l[r];
           }
+          auto update = [&](int cb, int ce) {
 #pragma unroll
-          for (int r = 0; r < kRpt; ++r) {
-            if (!act[r]) continue;        // rows that left keep their values
-            const double l = a[r][jj] / uc[jj];
-            a[r][jj] = l;
+            for (int c = cb; c < ce; ++c) {
+              const double uc = lane_value(u, c);
 #pragma unroll
-            for (int c = jj + 1; c < kSub; ++c) a[r][c] = fma(-l, uc[c], a[r][c]);
+              for (int r = 0; r < RPT; ++r) a[r][c] = fma(-l[r], uc, a[r][c]);
+            }
+          };
+          update(jj + 1, kSub);
 #pragma unroll
-            for (int b = 1; b < kPw / kSub; ++b)
-              if (q + b < kPw / kSub) {
-#pragma unroll
-                for (int c = b * kSub; c < (b + 1) * kSub; ++c) a[r][c] = fma(-l, uc[c], a[r][c]);
-              }
-          }
+          for (int b = 1; b < kPw / kSub; ++b)
+            if (q + b < kPw / kSub) update(b * kSub, (b + 1) * kSub);
         }
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) x[r] = a[r][jj + 1];
+        search(x);
       }
     }
 #pragma unroll
-    for (int r = 0; r < kRpt; ++r) {
+    for (int r = 0; r < RPT; ++r) {
       double t[kSub];
 #pragma unroll
       for (int c = 0; c < kSub; ++c) t[c] = a[r][c];
@@ -339,21 +383,21 @@ __global__ __launch_bounds__(kThreads) void piv_panel_kernel(
       for (int c = 0; c < kSub; ++c) a[r][kPw - kSub + c] = t[c];
     }
   }
+  // the rows below the panel's triangle, and the L part of the pivot rows
 #pragma unroll
-  for (int r = 0; r < kRpt; ++r) {
-    const int lr = g * kRows + r * kThreads + tid;
-    if (lr >= h) continue;
+  for (int r = 0; r < RPT; ++r) {
+    const int lr = g * (kThreads * RPT) + r * kThreads + tid;
     double* dst = A + (r0 + pos[r]) * lda + c0;
-    if (vec) {
+    if (act[r] && vec) {
 #pragma unroll
       for (int c = 0; c < kPw; c += 2) *reinterpret_cast<D2*>(dst + c) = D2{a[r][c], a[r][c + 1]};
-    } else {
+    } else if (lr < h) {
+      const int last = act[r] ? w : pos[r];
 #pragma unroll
       for (int c = 0; c < kPw; ++c)
-        if (c < w) dst[c] = a[r][c];
+        if (c < last) dst[c] = a[r][c];
     }
-    if (pos[r] < w) mv->src[pos[r]] = lr;
-    if (lr < w) mv->dst[lr] = pos[r];
+    if (act[r] && lr < w) mv->dst[lr] = pos[r];
   }
   __syncthreads();
   if (g == 0 && tid < w) ipiv[c0 + tid] = r0 + piv[tid];
@@ -372,33 +416,40 @@ __global__ __launch_bounds__(kMoveCols) void panel_apply_kernel(double* __restri
                                                                 int64_t lda, int64_t n,
                                                                 int64_t c0, int w, int64_t e0,
                                                                 const Moves* __restrict__ mv) {
-  __shared__ __attribute__((aligned(16))) double Ls[kPw][kPw];
+  typedef double D2 __attribute__((ext_vector_type(2)));
+  __shared__ __attribute__((aligned(16))) double Lt[kPw][kPw];   // Lt[p][i] = l_ip
   const int64_t t = (int64_t)blockIdx.x * kMoveCols + threadIdx.x;
   const int64_t col = t < c0 ? t : t + w;
   const bool live = col < n;
   const bool inside = live && col >= c0 + w && col < e0;
   const bool any = __any(inside);
-  if (any) {
-    for (int e = threadIdx.x; e < kPw * kPw; e += kMoveCols) {
-      const int i = e / kPw, p = e % kPw;
-      Ls[i][p] = (i < w && p < i) ? A[(c0 + i) * lda + c0 + p] : 0.0;
-    }
-  }
   double* __restrict__ P = A + c0 * lda + (live ? col : 0);
   double x[kPw], y[kPw];
 #pragma unroll
   for (int i = 0; i < kPw; ++i) x[i] = i < w ? P[(int64_t)mv->src[i] * lda] : 0.0;
 #pragma unroll
   for (int i = 0; i < kPw; ++i) y[i] = i < w ? P[(int64_t)i * lda] : 0.0;
+  if (any) {
+    double l[kPw * kPw / kMoveCols];
+#pragma unroll
+    for (int e = 0; e < kPw * kPw / kMoveCols; ++e) {
+      const int i = (e * kMoveCols + threadIdx.x) / kPw, p = threadIdx.x % kPw;
+      l[e] = (i < w && p < i) ? A[(c0 + i) * lda + c0 + p] : 0.0;
+    }
+#pragma unroll
+    for (int e = 0; e < kPw * kPw / kMoveCols; ++e)
+      Lt[threadIdx.x % kPw][(e * kMoveCols + threadIdx.x) / kPw] = l[e];
+  }
   __syncthreads();
   if (inside) {
 #pragma unroll
-    for (int i = 1; i < kPw; ++i) {
-      double acc = x[i];
+    for (int p = 0; p + 1 < kPw; ++p)
 #pragma unroll
-      for (int p = 0; p < i; ++p) acc = fma(-Ls[i][p], x[p], acc);
-      x[i] = acc;
-    }
+      for (int i = (p + 1) & ~1; i < kPw; i += 2) {
+        const D2 l = *reinterpret_cast<const D2*>(&Lt[p][i]);
+        if (i > p) x[i] = fma(-l.x, x[p], x[i]);
+        x[i + 1] = fma(-l.y, x[p], x[i + 1]);
+      }
   }
   if (!live) return;
 #pragma unroll
@@ -550,6 +601,25 @@ hipError_t prod(const double* A, int64_t lda, const double* B, int64_t ldb, doub
                : launch_gemm<double, double, double, float, 128, 128, 2, 2, false>(p, 1, s);
 }
 
+// One panel.  Rows per thread and workgroups: one workgroup while the rows fit
+// (no meeting); then one row per thread while every wave has at most one
+// candidate to wait for, because a step's update and LDS traffic grow with
+// the rows per thread; two beyond that, to bound the candidates to read.
+template <int RPT, bool MULTI>
+hipError_t launch_panel(double* A, int64_t lda, int64_t c, int h, int w, int64_t* ipiv,
+                        unsigned long long* slots, Words* words, Moves* mv, hipStream_t s) {
+  if constexpr (!MULTI) {
+    piv_panel_kernel<RPT, false><<<1, kThreads, 0, s>>>(A, lda, c, c, h, w, ipiv, slots, words, mv);
+    return hipGetLastError();
+  } else {
+    int64_t r0 = c, cc = c;
+    void* args[] = {&A, &lda, &r0, &cc, &h, &w, &ipiv, &slots, &words, &mv};
+    return hipLaunchCooperativeKernel(
+        reinterpret_cast<const void*>(piv_panel_kernel<RPT, true>),
+        dim3((unsigned)ceil_div(h, kThreads * RPT)), dim3(kThreads), args, 0, s);
+  }
+}
+
 trsm_status factor(int64_t n, double* A, int64_t lda, const Layout& L, int64_t* ipiv,
                    double* Linv, char* ws, hipStream_t s) {
   const int64_t nb = L.nb;
@@ -565,7 +635,7 @@ trsm_status factor(int64_t n, double* A, int64_t lda, const Layout& L, int64_t* 
   // words: bad = all ones, err = 0; no slot carries a step number of this call
   PIV_HIP(launch_fill_u32((unsigned*)words, 2, 0xFFFFFFFFu, s));
   PIV_HIP(launch_fill_u32((unsigned*)words + 2, 2, 0u, s));
-  if (n > kRows)
+  if (n > kThreads * kMaxRpt)
     PIV_HIP(launch_fill_u32((unsigned*)slots, (int64_t)4 * kMaxGroups * kSlotWords, 0u, s));
   trsm_plan_t plan = nullptr;
   PIV_TRY(trsm_plan(nb, 1, TRSM_F64, nb, 0, &plan));
@@ -574,18 +644,16 @@ trsm_status factor(int64_t n, double* A, int64_t lda, const Layout& L, int64_t* 
     const int64_t c0 = j * nb, sb = std::min(nb, n - c0), e0 = c0 + sb;
     hipError_t e = hipSuccess;
     for (int64_t c = c0; c < e0 && e == hipSuccess; c += kPw) {
-      int w = (int)std::min<int64_t>(kPw, e0 - c);
-      int h = (int)(n - c);
-      const int G = (h + kRows - 1) / kRows;
-      if (G == 1) {
-        piv_panel_kernel<false><<<1, kThreads, 0, s>>>(A, lda, c, c, h, w, ipiv, slots, words, mv);
-        e = hipGetLastError();
-      } else {
-        int64_t r0 = c, cc = c;
-        void* args[] = {&A, &lda, &r0, &cc, &h, &w, &ipiv, &slots, &words, &mv};
-        e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(piv_panel_kernel<true>),
-                                       dim3(G), dim3(kThreads), args, 0, s);
-      }
+      const int w = (int)std::min<int64_t>(kPw, e0 - c);
+      const int h = (int)(n - c);
+      if (h <= kThreads)
+        e = launch_panel<1, false>(A, lda, c, h, w, ipiv, slots, words, mv, s);
+      else if (h <= 2 * kThreads)
+        e = launch_panel<2, false>(A, lda, c, h, w, ipiv, slots, words, mv, s);
+      else if (h <= kWaves * kThreads)
+        e = launch_panel<1, true>(A, lda, c, h, w, ipiv, slots, words, mv, s);
+      else
+        e = launch_panel<2, true>(A, lda, c, h, w, ipiv, slots, words, mv, s);
       // the panel's exchanges in all other columns, U of the panel rows in the
       // block's remaining columns, then the block's trailing rows
       if (e == hipSuccess && n > w) {
