@@ -335,6 +335,9 @@ constexpr int vmcnt_imm(int n) {
   return (n & 0xF) | (((n >> 4) & 3) << 14) | (0x7 << 4) | (0xF << 8);
 }
 
+// s_waitcnt immediate that waits for every vector-memory and LDS operation.
+constexpr int kWaitAll = 0x7 << 4;
+
 // Matrix-core tile with operands copied from HBM straight into LDS by
 // buffer loads (no register staging), two LDS stages, one barrier per chunk.
 // For one-k-per-lane instructions (binary64, binary32) and 16-byte aligned
@@ -347,7 +350,13 @@ constexpr int vmcnt_imm(int n) {
 //    bytes of padding;
 //  * B given as B^T (BKMAJOR true: N rows of K, k contiguous): BN rows of
 //    128 bytes swizzled like A, and read like A.
-// All fragments of a half-chunk are read before its MFMAs are issued.
+// A half-chunk's fragments are read one half ahead of their MFMAs, across the
+// chunk boundary too: the second half while the first multiplies, and the
+// next chunk's first half, after the one barrier per chunk, while the second
+// multiplies.  At that barrier every wave holds both halves of chunk c, so its
+// stage is free for chunk c + 2 and two stages keep a whole chunk time between
+// a copy and its use.  (Reading each half right before its MFMAs left the
+// matrix cores idle for two LDS latencies per chunk.)
 // Triangular masks are applied to the fragments, only in chunks that cross
 // the diagonal.
 template <typename TIn, typename TCin, typename TCout, typename TC2, int BM, int BN, int WGM,
@@ -380,7 +389,8 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout,
   static_assert(!BKMAJOR || BT_INST * NW * 8 == BN, "even split of B^T loads");
   __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN, gi = lane & 15, g = lane >> 4;
   const int zo = z / p.zdiv, zi = z % p.zdiv;
   const TIn* __restrict__ A = p.A + zo * p.sa_o + zi * p.sa_i;
@@ -390,7 +400,7 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout,
   int kbeg;
   int nchunks = chunk_range<BM, BK>(K, p.flags, r0, c0, kbeg);
   nchunks = split_range<BK>(K, s, p.ksplit, nchunks, kbeg);
-  const bool a_lower = p.flags & G_A_LOWER;
+  const bool a_lower = (p.flags & G_A_LOWER) && !(p.flags & G_A_ZERO_UPPER);
   const bool b_lower = p.flags & G_B_LOWER;
 
   Out acc[TM][TN];
@@ -401,8 +411,15 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout,
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[i][j][r] = Acc(0);
 
+  // Copies of chunk c into stage st.  The large tile issues past the last chunk
+  // too (RUNON: every lane's offset is then out of range, and zeros nobody reads
+  // arrive): without a branch the copies' instructions are scheduled among
+  // the MFMAs (n = k = 16384: 68.1 against 70.6 ms).  A small tile has few chunks
+  // and skips them.
+  constexpr bool RUNON = BM * BN >= 128 * 128;
   auto issue = [&](int c, int st) {
     const int k0 = kbeg + c * BK;
+    const int kend = !RUNON || c < nchunks ? K : 0;
     char* base = smem + st * STAGE;
     const __amdgpu_buffer_rsrc_t ra = make_rsrc(A + (int64_t)r0 * lda + k0);
 #pragma unroll
@@ -410,7 +427,7 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout,
       const int rb = 8 * (wave * A_INST + q);
       const int r = rb + (lane >> 3);
       const int d = (lane & 7) ^ (r & 7);
-      const bool ok = (r0 + r < M) && (k0 + d * VEC < K);
+      const bool ok = (r0 + r < M) && (k0 + d * VEC < kend);
       const int off = ok ? (r * lda + d * VEC) * ES : kBufOOB;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           ra, (__attribute__((address_space(3))) void*)(base + rb * 128), 16, off, 0, 0, 0);
@@ -422,7 +439,7 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout,
         const int rb = 8 * (wave * BT_INST + q);
         const int r = rb + (lane >> 3);
         const int d = (lane & 7) ^ (r & 7);
-        const bool ok = (c0 + r < N) && (k0 + d * VEC < K);
+        const bool ok = (c0 + r < N) && (k0 + d * VEC < kend);
         const int off = ok ? (r * ldb + d * VEC) * ES : kBufOOB;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
             rbt, (__attribute__((address_space(3))) void*)(base + A_BYTES + rb * 128), 16, off, 0,
@@ -436,75 +453,107 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout,
       const int qi = wave * B_INST + q;
       const int kr = qi * RPI + lane / (64 / RPI);
       const int cv = (lane % (64 / RPI)) * VEC;
-      const bool ok = (k0 + kr < K) && (c0 + cv < N);
+      const bool ok = (k0 + kr < kend) && (c0 + cv < N);
       const int off = ok ? (kr * ldb + cv) * ES : kBufOOB;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           rbs, (__attribute__((address_space(3))) void*)(base + A_BYTES + qi * (1024 + 16)), 16,
           off, 0, 0, 0);
     }
   };
-
-  if (nchunks > 0) issue(0, 0);
-  for (int c = 0; c < nchunks; ++c) {
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // this wave's part of chunk c has landed
-    __syncthreads();                            // ... everyone's; and chunk c-1 is consumed
-    if (c + 1 < nchunks) issue(c + 1, (c + 1) & 1);
+  // Fragments of half h (the lane group's h-th 16-byte piece of k) of chunk c.
+  struct Half {
+    V16 a[TM];
+    TIn b[VEC][TN];
+  };
+  auto fetch = [&](Half& f, int c, int h) {
     const char* as = smem + (c & 1) * STAGE;
     const char* bs = as + A_BYTES;
-    const int k0 = kbeg + c * BK;
-    const bool mask_a = a_lower && !(p.flags & G_A_ZERO_UPPER) && (k0 + BK - 1 > r0 + wm * WTM);
-    const bool mask_b = b_lower && (k0 < c0 + wn * WTN + WTN - 1);
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {               // the lane group's two 16-byte pieces of k
-      V16 fa[TM];
-      TIn fb[VEC][TN];
+    for (int i = 0; i < TM; ++i) {
+      const int r = wm * WTM + i * 16 + gi;
+      const int slot = (2 * g + h) ^ (r & 7);
+      f.a[i] = *reinterpret_cast<const V16*>(as + r * 128 + slot * 16);
+    }
+    if constexpr (BKMAJOR) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int r = wm * WTM + i * 16 + gi;
+      for (int j = 0; j < TN; ++j) {
+        const int r = wn * WTN + j * 16 + gi;
         const int slot = (2 * g + h) ^ (r & 7);
-        fa[i] = *reinterpret_cast<const V16*>(as + r * 128 + slot * 16);
+        const V16 v = *reinterpret_cast<const V16*>(bs + r * 128 + slot * 16);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) f.b[e][j] = v[e];
       }
-      if constexpr (BKMAJOR) {
+    } else {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int r = wn * WTN + j * 16 + gi;
-          const int slot = (2 * g + h) ^ (r & 7);
-          const V16 v = *reinterpret_cast<const V16*>(bs + r * 128 + slot * 16);
+      for (int e = 0; e < VEC; ++e) {
+        const int kr = g * KL + h * VEC + e;
 #pragma unroll
-          for (int e = 0; e < VEC; ++e) fb[e][j] = v[e];
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          const int kr = g * KL + h * VEC + e;
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-            fb[e][j] = *reinterpret_cast<const TIn*>(bs + (kr / RPI) * (1024 + 16) +
-                                                     (kr % RPI) * ROW_B +
-                                                     (wn * WTN + j * 16 + gi) * ES);
-        }
+        for (int j = 0; j < TN; ++j)
+          f.b[e][j] = *reinterpret_cast<const TIn*>(bs + (kr / RPI) * (1024 + 16) +
+                                                    (kr % RPI) * ROW_B +
+                                                    (wn * WTN + j * 16 + gi) * ES);
       }
-      if (mask_a) {
+    }
+  };
+  auto mask = [&](Half& f, int c, int h) {
+    const int k0 = kbeg + c * BK;
+    if (a_lower && k0 + BK - 1 > r0 + wm * WTM) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int e = 0; e < VEC; ++e)
-            if (k0 + g * KL + h * VEC + e > r0 + wm * WTM + i * 16 + gi) fa[i][e] = TIn(0);
-      }
-      if (mask_b) {
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int e = 0; e < VEC; ++e)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-            if (k0 + g * KL + h * VEC + e < c0 + wn * WTN + j * 16 + gi) fb[e][j] = TIn(0);
-      }
+          if (k0 + g * KL + h * VEC + e > r0 + wm * WTM + i * 16 + gi) f.a[i][e] = TIn(0);
+    }
+    if (b_lower && k0 < c0 + wn * WTN + WTN - 1) {
 #pragma unroll
       for (int e = 0; e < VEC; ++e)
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j) acc[i][j] = MF::mma(fa[i][e], fb[e][j], acc[i][j]);
+        for (int j = 0; j < TN; ++j)
+          if (k0 + g * KL + h * VEC + e < c0 + wn * WTN + j * 16 + gi) f.b[e][j] = TIn(0);
     }
+  };
+  auto multiply = [&](const Half& f) {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = MF::mma(f.a[i][e], f.b[e][j], acc[i][j]);
+  };
+
+  if (nchunks > 0) {
+    constexpr int LPC = A_INST + (BKMAJOR ? BT_INST : B_INST);   // copies per wave and chunk
+    Half f0, f1;
+    issue(0, 0);
+    if (RUNON || nchunks > 1) {
+      issue(1, 1);
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(LPC));   // this wave's part of chunk 0 has landed
+    } else {
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    }
+    __syncthreads();                                // ... everyone's
+    fetch(f0, 0, 0);
+    const bool masked = a_lower || b_lower;
+    for (int c = 0; c < nchunks; ++c) {
+      // the reads go out before the MFMAs (the scheduler would sink them)
+      fetch(f1, c, 1);
+      __builtin_amdgcn_sched_barrier(0);
+      if (masked) mask(f0, c, 0);
+      multiply(f0);
+      // both halves of chunk c are in registers and chunk c + 1 has landed,
+      // for every wave: its stage takes chunk c + 2
+      if (RUNON || c + 1 < nchunks) {
+        __builtin_amdgcn_s_waitcnt(kWaitAll);
+        __syncthreads();
+      }
+      if (RUNON || c + 1 < nchunks) fetch(f0, c + 1, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (RUNON || c + 2 < nchunks) issue(c + 2, c & 1);
+      if (masked) mask(f1, c, 1);
+      multiply(f1);
+    }
+    // RUNON's last copies: nothing may still be writing the stages
+    if (RUNON) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
   }
   gemm_epilogue<TIn, TCin, TCout, TC2, TM, TN, WTM, WTN>(p, acc, zo, zi, z, s, r0, c0, wm, wn, g,
                                                         gi);
@@ -759,6 +808,135 @@ __device__ __forceinline__ void gemm_tile(const GemmParams<TIn, TCin, TCout, TC2
   }
 }
 
+// Small products straight from global memory to registers: one wave computes a
+// 16 x 16 tile, four waves a workgroup.  KW = 1: the waves take a 2 x 2 group of
+// tiles and share operand rows in the unit's cache; KW = 4: they take the
+// quarters of K of one tile, summed in a fixed order through LDS.  Such a
+// product is bound by its chain, not by its work: no staging, no barrier per
+// chunk, the loads of 32 (binary64) or 64 (binary32) k in flight while the previous
+// ones multiply, and four times as many workgroups as 64 x 64 tiles.  VEC16:
+// operands with contiguous k are read 16 bytes at a time (aligned); otherwise
+// one element at a time, any alignment.  Triangles are skipped and masked per
+// 16 x 16 tile.  C must not overlap A or B.
+template <typename TIn, typename TCin, typename TCout, typename TC2, bool BKMAJOR, bool VEC16,
+          int KW>
+__global__ __launch_bounds__(256) void gemm_direct_kernel(GemmParams<TIn, TCin, TCout, TC2> p) {
+  using MF = Mfma<TIn>;
+  using Out = typename MF::Out;
+  using V16 = typename VecOf<TIn>::T2;
+  constexpr int VEC = 16 / (int)sizeof(TIn);   // k per lane and step
+  constexpr int SK = 4 * VEC;                  // k per step of the wave
+  constexpr int U = 4;                         // steps in flight
+  static_assert(MF::kPerLane == 1, "one k per lane and instruction");
+  const int lane = threadIdx.x & 63, gi = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int z = blockIdx.z, zo = z / p.zdiv, zi = z % p.zdiv;
+  const int M = p.M, N = p.N, K = p.K;
+  const int ntn = (N + 15) / 16, ntm = (M + 15) / 16;
+  int tm, tn;
+  if (KW == 1) {
+    const int gn = (ntn + 1) / 2;
+    tm = 2 * ((int)blockIdx.x / gn) + (wave >> 1);
+    tn = 2 * ((int)blockIdx.x % gn) + (wave & 1);
+  } else {
+    tm = (int)blockIdx.x / ntn;
+    tn = (int)blockIdx.x % ntn;
+  }
+  const bool c_lower = p.flags & G_C_LOWER;
+  if (KW == 1 && (tm >= ntm || tn >= ntn || (c_lower && tn > tm))) return;
+  if (KW > 1 && c_lower && tn > tm) return;
+  const int r0 = tm * 16, c0 = tn * 16;
+  const bool a_mask = (p.flags & G_A_LOWER) && !(p.flags & G_A_ZERO_UPPER);
+  const bool b_mask = p.flags & G_B_LOWER;
+  int kend = K, kbeg = 0;
+  if (p.flags & G_A_LOWER) kend = min(K, r0 + 16);
+  if (p.flags & G_A_UPPER) kbeg = min(r0, K) / SK * SK;
+  if (p.flags & G_B_LOWER) kbeg = min(c0, K) / SK * SK;
+  int steps = kend > kbeg ? (kend - kbeg + SK - 1) / SK : 0;
+  if (KW > 1) {
+    const int per = (steps + KW - 1) / KW, first = wave * per;
+    kbeg += min(first, steps) * SK;
+    steps = max(0, min(per, steps - first));
+  }
+  const int row = min(r0 + gi, M - 1), col = min(c0 + gi, N - 1);
+  const TIn* __restrict__ A = p.A + zo * p.sa_o + zi * p.sa_i + (int64_t)row * p.lda;
+  const TIn* __restrict__ B = p.B + zo * p.sb_o + zi * p.sb_i +
+                              (BKMAJOR ? (int64_t)col * p.ldb : (int64_t)col);
+  struct Step {
+    TIn a[VEC], b[VEC];
+  };
+  // the lane group's VEC consecutive k of one step
+  auto load = [&](Step& f, int k0) {
+    const int k = k0 + g * VEC;
+    if (k0 + SK <= K) {
+      if (VEC16) {
+        const V16 v = *reinterpret_cast<const V16*>(A + k);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) f.a[e] = v[e];
+      } else {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) f.a[e] = A[k + e];
+      }
+      if (BKMAJOR && VEC16) {
+        const V16 v = *reinterpret_cast<const V16*>(B + k);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) f.b[e] = v[e];
+      } else {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) f.b[e] = BKMAJOR ? B[k + e] : B[(int64_t)(k + e) * p.ldb];
+      }
+    } else {   // the last, partial step: zeros past K
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        const bool ok = k + e < K;
+        const int64_t q = ok ? k + e : 0;
+        const TIn va = A[q], vb = BKMAJOR ? B[q] : B[q * p.ldb];
+        f.a[e] = ok ? va : TIn(0);
+        f.b[e] = ok ? vb : TIn(0);
+      }
+    }
+  };
+  auto mask = [&](Step& f, int k0) {
+    const int k = k0 + g * VEC;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+      if (a_mask && k + e > r0 + gi) f.a[e] = TIn(0);
+      if (b_mask && k + e < c0 + gi) f.b[e] = TIn(0);
+    }
+  };
+  Out acc[1][1] = {};
+  Step f[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (u < steps) load(f[u], kbeg + u * SK);
+  for (int t = 0; t < steps; t += U) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (t + u < steps) {
+        const int k0 = kbeg + (t + u) * SK;
+        if (a_mask || b_mask) mask(f[u], k0);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) acc[0][0] = MF::mma(f[u].a[e], f[u].b[e], acc[0][0]);
+        if (t + u + U < steps) load(f[u], k0 + U * SK);
+      }
+    }
+  }
+  if (KW > 1) {
+    __shared__ typename MF::Acc part[KW > 1 ? KW - 1 : 1][64][4];
+    if (wave > 0) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) part[wave - 1][lane][r] = acc[0][0][r];
+    }
+    __syncthreads();
+    if (wave > 0) return;
+#pragma unroll
+    for (int w = 0; w + 1 < KW; ++w)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[0][0][r] += part[w][lane][r];
+  }
+  gemm_epilogue<TIn, TCin, TCout, TC2, 1, 1, 16, 16>(p, acc, zo, zi, z, 0, r0, c0, 0, 0, g, gi);
+}
+
 template <typename TIn, typename TCin, typename TCout, typename TC2,
           int BM, int BN, int WGM, int WGN, bool BKMAJOR, bool ALIGNED, bool CLOWER = false>
 __global__ __launch_bounds__(WGM * WGN * 64, 2)
@@ -833,11 +1011,11 @@ inline bool gemm_aligned(const P& p) {
          (BKMAJOR || p.N % VEC == 0) && span_a < kBufOOB && span_b < kBufOOB;
 }
 
-// Split-K policy: products with at most half a round of workgroups split K
-// into S slices (each at least kSplitMinChunks chunks) so that at most one
-// round runs (kSplitTarget = two 128 x 128 workgroups per compute unit), as
-// far as the scratch in p.part holds the partial products.  Without scratch
-// (p.part null) nothing is split.
+// Split-K policy: products with at most half of `target` workgroups split K into
+// S slices (each at least kSplitMinChunks chunks) so that at most `target`
+// workgroups run, as far as the scratch in p.part holds the partial products.
+// Without scratch (p.part null) nothing is split.  The target is kSplitTarget,
+// two 128 x 128 workgroups per compute unit.
 constexpr int kSplitTarget = 512;
 constexpr int kSplitMinChunks = 4;
 constexpr int kSplitMax = 16;
@@ -853,6 +1031,86 @@ inline int gemm_ksplit(const P& p, int64_t wgs, int batch, int target) {
   return S > 1 ? (int)S : 1;
 }
 
+// Whether a small binary64/binary32 product takes gemm_direct_kernel.  Its rate
+// is that of the caches, about 10.7 (binary64) or 20 (binary32) 16x16x4 matrix
+// instructions per ns however they are spread, after about 3.5 us; a 64 x 64
+// tile takes 4 us and about 0.7 us per 128 bytes of K (binary32: 0.4 us per 16
+// k) however few tiles there are, or, split over K, 13 us with its finish pass
+// and then 23 instructions per ns.  The line lies where the two meet.  Measured
+// direct / 64 x 64 (best of split and not), binary64: 128^3 triangular 3.7 /
+// 12.9 us, 512^3 triangular 10.7 / 19.8, 1024 x 128 x 1024 triangular 12.0 /
+// 18.9, 3968 x 128 x 128 9.5 / 10.1, 2048 x 128 x 1024 26.5 / 24.8, 1024 x 1024 x
+// 128 15.6 / 11.0.  C may be neither A nor B: another workgroup would read
+// what one has overwritten.
+template <typename TIn, typename P>
+inline bool direct_ok(const P& p, int batch) {
+  if ((const void*)p.Cout == (const void*)p.A || (const void*)p.Cout == (const void*)p.B)
+    return false;
+  int64_t tiles = (int64_t)((p.M + 15) / 16) * ((p.N + 15) / 16) * batch;
+  int64_t steps = (p.K + 3) / 4;
+  if (p.flags & G_C_LOWER) tiles = (tiles + 1) / 2;
+  if (((p.flags & (G_A_LOWER | G_A_UPPER)) && p.M == p.K) ||
+      ((p.flags & G_B_LOWER) && p.N == p.K))
+    steps = (steps + 1) / 2;
+  const int64_t most = sizeof(TIn) == 8 ? 192 * 1024 : 256 * 1024;
+  return tiles * steps <= std::min<int64_t>(most, (int64_t)512 * p.K);
+}
+
+// Launch of gemm_direct_kernel (the caller has checked direct_ok).  K is split
+// over a workgroup's waves unless there are many tiles or hardly any steps.
+template <typename TIn, typename TCin, typename TCout, typename TC2, bool BKMAJOR>
+inline hipError_t launch_direct(const GemmParams<TIn, TCin, TCout, TC2>& p, int batch,
+                                hipStream_t stream, int kw = 0) {
+  GemmParams<TIn, TCin, TCout, TC2> q = p;
+  q.ksplit = 1;
+  const unsigned ntm = (unsigned)((p.M + 15) / 16), ntn = (unsigned)((p.N + 15) / 16);
+  if (kw == 0)
+    kw = (int64_t)ntm * ntn * batch > 2048 || p.K * (int)sizeof(TIn) < 512 ? 1 : 4;
+  const dim3 grid(kw == 1 ? ((ntm + 1) / 2) * ((ntn + 1) / 2) : ntm * ntn, 1, (unsigned)batch);
+  constexpr int VEC = 16 / (int)sizeof(TIn);
+  auto al = [](const void* x) { return (reinterpret_cast<uintptr_t>(x) & 15) == 0; };
+  const bool vec = al(p.A) && p.lda % VEC == 0 && p.sa_o % VEC == 0 && p.sa_i % VEC == 0 &&
+                   (!BKMAJOR || (al(p.B) && p.ldb % VEC == 0 && p.sb_o % VEC == 0 &&
+                                 p.sb_i % VEC == 0));
+  auto go = [&](auto kernel) { kernel<<<grid, 256, 0, stream>>>(q); };
+  if (kw == 1) {
+    if (vec) go(gemm_direct_kernel<TIn, TCin, TCout, TC2, BKMAJOR, true, 1>);
+    else go(gemm_direct_kernel<TIn, TCin, TCout, TC2, BKMAJOR, false, 1>);
+  } else {
+    if (vec) go(gemm_direct_kernel<TIn, TCin, TCout, TC2, BKMAJOR, true, 4>);
+    else go(gemm_direct_kernel<TIn, TCin, TCout, TC2, BKMAJOR, false, 4>);
+  }
+  return hipGetLastError();
+}
+
+// K slices of a product of `wgs` 64 x 64 tiles on the direct-to-LDS path: the S
+// with the least modelled time.  A chunk (128 bytes of K) takes about 0.70 us
+// (binary64) or 0.9 us (binary32) a workgroup per compute unit, one or several on
+// it, so the tiles take as long as the fullest of 256 units; the finish pass
+// of a split takes 4 us and reads and writes S + 2 times C at 3 TB/s.  Measured at
+// N = 128, K = 1024, binary64: 480 workgroups (M = 15360) 89 us unsplit and 95 in
+// two, 256 (8192) 49 and 54, 64 (2048) 45 and, in eight, 25.
+template <typename TIn, typename P>
+inline int chain_ksplit(const P& p, int64_t wgs, int batch) {
+  if (!p.part) return 1;
+  constexpr int BK = 128 / sizeof(TIn);
+  const int64_t nck = (p.K + BK - 1) / BK;
+  const int64_t per = (int64_t)p.M * p.N * batch * (int64_t)sizeof(typename Mfma<TIn>::Acc);
+  const double chunk = sizeof(TIn) == 8 ? 0.70 : 0.9;
+  int best = 1;
+  double least = 1e300;
+  for (int64_t S = 1; S <= kSplitMax; ++S) {
+    if (S > 1 && (nck / S < kSplitMinChunks || S * per > p.part_bytes)) break;
+    const double t = (double)((wgs * S + 255) / 256) * (double)((nck + S - 1) / S) * chunk +
+                     (S > 1 ? 4.0 + (double)(S + 2) * (double)per / 3e6 : 0.0);
+    if (t < least) {
+      least = t;
+      best = (int)S;
+    }
+  }
+  return best;
+}
+
 // Host-side launch helper.  Picks the aligned (16-byte vector) path when every
 // operand start, leading dimension and batch stride allows it.
 template <typename TIn, typename TCin, typename TCout, typename TC2,
@@ -861,13 +1119,19 @@ inline hipError_t launch_gemm(const GemmParams<TIn, TCin, TCout, TC2>& p, int ba
                               hipStream_t stream) {
   if (p.M <= 0 || p.N <= 0 || batch <= 0) return hipSuccess;
   if ((p.flags & G_C_LOWER) && (p.M != p.N || BM != BN)) return hipErrorInvalidValue;
+  if constexpr (BM == 64 && BN == 64 && Mfma<TIn>::kPerLane == 1) {
+    if (direct_ok<TIn>(p, batch))
+      return launch_direct<TIn, TCin, TCout, TC2, BKMAJOR>(p, batch, stream);
+  }
   const bool aligned = gemm_aligned<TIn, BM, BN, BKMAJOR>(p);
   const int64_t tiles = gemm_wgs(p.M, p.N, p.K, p.flags, BM, BN);
   GemmParams<TIn, TCin, TCout, TC2> q = p;
   // one round of workgroups: two per compute unit for the 128 x 128 tiles,
   // four for the smaller ones (their registers and LDS allow it)
   const int target = (BM * BN >= 128 * 128) ? kSplitTarget : 2 * kSplitTarget;
-  q.ksplit = gemm_ksplit<TIn>(p, tiles * batch, batch, target);
+  const bool chain = BM * BN < 128 * 128 && aligned && Mfma<TIn>::kPerLane == 1;
+  q.ksplit = chain ? chain_ksplit<TIn>(p, tiles * batch, batch)
+                   : gemm_ksplit<TIn>(p, tiles * batch, batch, target);
   // lower-triangle products take their own instantiation (tile enumeration)
   const bool clower = p.flags & G_C_LOWER;
   dim3 grid((unsigned)tiles, (unsigned)q.ksplit, (unsigned)batch);

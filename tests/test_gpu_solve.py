@@ -71,6 +71,38 @@ def test_ragged_shapes(torch, T, n, k, n0):
     assert err <= TOL64
 
 
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("n,k,n0,pad", [(17, 1, 16, 0), (33, 15, 16, 1), (130, 17, 64, 3),
+                                        (200, 16, 128, 0), (1000, 33, 256, 1), (95, 31, 32, 0),
+                                        (1030, 66, 512, 2), (700, 400, 512, 0)])
+@pytest.mark.parametrize("problem", ["lower", "transpose", "upper"])
+def test_small_products_at_tile_edges(torch, T, problem, n, k, n0, pad, prec):
+    # the products of small systems take 16 x 16 tiles straight from global
+    # memory (K split over a workgroup's waves or not) or 64 x 64 tiles: rows,
+    # columns and K one past or short of a tile, aligned and unaligned leading
+    # dimensions, dense, lower and upper triangular operands; nothing outside
+    # the matrices is read (NaN) or written
+    dt = torch.float64 if prec == "f64" else torch.float32
+    L, B = gen.easy_system(n, k, 3 * n + k, upper=np.nan)
+    if prec == "f32":
+        L, B = L.astype(np.float32).astype(np.float64), B.astype(np.float32).astype(np.float64)
+    Lf = torch.full((n, n + pad), float("nan"), dtype=dt, device="cuda")
+    Lf[:, :n] = dev(torch, L.T if problem == "upper" else L, dt)
+    Bf = torch.full((n, k + pad), float("nan"), dtype=dt, device="cuda")
+    Bf[:, :k] = dev(torch, B, dt)
+    Xf = torch.full((n, k + pad), -7.0, dtype=dt, device="cuda")
+    flags = {"lower": 0, "transpose": T.FLAG_TRANSPOSE, "upper": T.FLAG_UPPER}[problem]
+    s = T.Solver.create(n, k, prec, n0, flags)
+    s.invert(Lf[:, :n])
+    s.solve(Lf[:, :n], Bf[:, :k], X=Xf[:, :k])
+    torch.cuda.synchronize()
+    s.close()
+    ref = oracle.trsm(L, B) if problem == "lower" else oracle.trsm_t(L, B)
+    err = oracle.rel_fro_err(host(Xf[:, :k]), ref)
+    assert err <= (TOL64 if prec == "f64" else TOL32)
+    assert bool((Xf[:, k:] == -7.0).all())
+
+
 @pytest.mark.parametrize("n,k", [(0, 5), (6, 0), (0, 0)])
 def test_empty_systems_are_no_ops(torch, T, n, k):
     # nothing to solve: every call succeeds without touching memory (null
