@@ -173,9 +173,13 @@ def test_panel_workgroup_edges_match_the_oracle(torch, T, n, nb, pad):
     F = buf[:, :n].cpu().numpy()
     assert st == T.OK and idx == -1 and fail == -1
     assert np.array_equal(f.ipiv.cpu().numpy(), po)
-    # the same tolerance as the oracle comparison at these sizes above
-    assert np.abs(np.tril(F, -1) - np.tril(Lo, -1)).max() <= 1e-11
-    assert np.abs(np.triu(F) - Uo).max() <= 1e-11 * np.abs(Uo).max()
+    # backward error, which does not depend on how ill-conditioned the last
+    # Schur complements of the scaled rows are (their factor entries differ
+    # between two correct eliminations by 1e-12 to 1e-11 here)
+    L, Um = np.tril(F, -1) + np.eye(n), np.triu(F)
+    assert np.abs(np.tril(F, -1)).max() <= 1.0
+    p = oracle.perm_from_ipiv(po)
+    assert np.linalg.norm(A[p] - L @ Um) / np.linalg.norm(A) <= 8 * n * U64
     assert bool(torch.isnan(buf[:, n:]).all())
 
 
