@@ -1,10 +1,11 @@
-// Non-GEMM kernels of the gfx950 triangular solver: diagonal-block
-// extraction, the LDS leaf of the recursive triangular inversion, the
-// substitution leaf of the recursive baseline, precision conversions and
+// Non-GEMM kernels of the gfx950 triangular solver: the LDS base case of the
+// recursive triangular inversion, the substitution leaf of the recursive baseline, precision conversions and
 // deterministic norm reductions.
 #include "kernels.hpp"
 
 #include <math.h>
+
+#include "diag.hpp"
 
 namespace trsm {
 
@@ -21,93 +22,164 @@ inline unsigned grid_for(int64_t work, int threads, int64_t cap = 1 << 20) {
 }
 
 // ---------------------------------------------------------------------------
-// Alg. Diagonal-Inverter, data movement: the block diagonal L_D is copied
-// into its own packed buffer (one n0 x n0 binary64 block per S_i).
+// Alg. Diagonal-Inverter: every diagonal block S_b of L becomes a packed n0 x n0
+// binary64 block of Linv, worked on in squares of ts = min(n0, 128) rows, one
+// workgroup each.  An off-diagonal square of the lower triangle is copied.  A
+// diagonal one is inverted in LDS, the base case of Alg. RecTriInv (4 x 4 blocks
+// by substitution, then its combine for 4 to 64 rows on the matrix cores); zeros
+// above its diagonal.
+// Positions past row/column n hold the identity.  With `upper`, L is an
+// upper-triangular U read transposed; with `unit` its diagonal is one.
+// The first workgroup starts the status word.
+// Measured: 8 us for one square of 64 rows and 15 for one of 128; extraction, a
+// 64-row leaf by substitution and (128 rows) two combine launches took 44 and 58.
+// All of n = 16384 in squares of 128: 21 us.
 // ---------------------------------------------------------------------------
-template <typename TL>
-__global__ __launch_bounds__(256) void extract_diag_kernel(const TL* __restrict__ L, int64_t ldl,
-                                                           int64_t n, int64_t n0,
-                                                           double* __restrict__ Linv,
-                                                           unsigned long long* bad, bool upper) {
-  // one row of one packed block per workgroup (row index b n0 + i is also
-  // the global row of L), threads along its columns
-  const int64_t gr = blockIdx.x;
-  const int64_t b = gr / n0, i = gr - b * n0;
-  double* __restrict__ out = Linv + gr * n0;
-  for (int64_t j = threadIdx.x; j < n0; j += blockDim.x) {
-    const int64_t gc = b * n0 + j;
-    double v;
-    if (gr < n && gc < n) {
-      v = (j <= i) ? static_cast<double>(upper ? L[gc * ldl + gr] : L[gr * ldl + gc]) : 0.0;
-      if (i == j && (!(v != 0.0) || !isfinite(v))) atomicMin(bad, (unsigned long long)gr);
-    } else {
-      v = (i == j) ? 1.0 : 0.0;
-    }
-    out[j] = v;
-  }
-}
+constexpr int kInvNt = kInvRows / 16;
+constexpr int kInvThreads = 1024;       // a wave for each tile of the largest combine
 
-// ---------------------------------------------------------------------------
-// Alg. RecTriInv base case ("sequential inversion"): the nb x nb leaf is
-// inverted by substitution on the identity.  Thread t owns column t of the
-// inverse, kept in registers:
-//   x[i] = (delta(i, t) - sum_{p<i} l[i][p] x[p]) / l[i][i],   i = 0 .. 63,
-// which is zero above the diagonal (i < t) and 1 / l[t][t] on it.  Every lane
-// reads the same l[i][p] (an LDS broadcast); the sum runs in four partial
-// sums.  Rows and columns at or beyond nb hold the identity.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void trtri_leaf_kernel(double* __restrict__ Linv, int64_t n0,
-                                                        int64_t nb, int64_t lpb) {
-  __shared__ __attribute__((aligned(16))) double Ls[64][64];
-  const int64_t leaf = blockIdx.x;
-  const int64_t b = leaf / lpb, q = leaf % lpb;
-  double* P = Linv + b * n0 * n0 + q * nb * (n0 + 1);
-  const int t = threadIdx.x;
-  for (int i = 0; i < 64; ++i) {
-    double v;
-    if (i < nb && t < nb) v = (t <= i) ? P[(int64_t)i * n0 + t] : 0.0;
-    else v = (i == t) ? 1.0 : 0.0;
-    Ls[i][t] = v;
+// TS: the square's rows, or 0 for `small` of them (below kInvRows).
+template <typename TL, int TS>
+__global__ __launch_bounds__(kInvThreads) void block_inverse_kernel(
+    const TL* __restrict__ L, int64_t ldl, int64_t n, int64_t n0, int small, int64_t m,
+    double* __restrict__ Linv, unsigned long long* __restrict__ bad, bool upper, bool unit) {
+  using namespace diag;
+  using Map = LowerTiles;
+  __shared__ __attribute__((aligned(16))) double S[Map::count(kInvNt) * kTile];
+  const int ts = TS ? TS : small;
+  // workgroups: the diagonal squares first (they take longest), then the others
+  const int nt = (int)(n0 / ts), diagonals = (int)(m * nt), id = blockIdx.x, tid = threadIdx.x;
+  int b, ti, tj;
+  if (id < diagonals) {
+    b = id / nt;
+    ti = tj = id - b * nt;
+  } else {
+    const int per = nt * (nt - 1) / 2, e = id - diagonals;
+    b = e / per;
+    int q = e - b * per;
+    ti = 1;
+    while (q >= ti) q -= ti++;
+    tj = q;
+  }
+  if (bad && id == 0 && tid == 0) *bad = ~0ull;
+  const int64_t gr0 = b * n0 + (int64_t)ti * ts, gc0 = b * n0 + (int64_t)tj * ts;
+  double* __restrict__ out = Linv + b * n0 * n0 + (int64_t)ti * ts * n0 + (int64_t)tj * ts;
+  const int lg = 31 - __builtin_clz(ts);
+  // A thread's elements: `fast` along L's rows in memory, `slow` = s0 + q ds.
+  const int fast = tid & (ts - 1), s0 = tid >> lg, ds = kInvThreads >> lg;
+  constexpr int kEach = kInvRows * kInvRows / kInvThreads;
+  const int64_t slow0 = upper ? gc0 : gr0, fast0 = upper ? gr0 : gc0;
+  const int slows = (int)min((int64_t)ts, n - slow0), fasts = (int)min((int64_t)ts, n - fast0);
+  const bool diagonal = ti == tj;
+  // The slow indexes a thread reads, [lo, hi).  All its loads go out before the
+  // first is used; a load outside is clamped to the square's first element (a
+  // predicated load would be waited for before the next), and pointers advance by
+  // a uniform step (a 64-bit product an element cost 36 instructions a load, more
+  // than the memory's latency).
+  const int lo = diagonal && !upper ? fast : 0;
+  const int hi = fast >= fasts ? 0 : diagonal && upper ? min(slows, fast + 1) : slows;
+  TL v[kEach];
+  {
+    const TL* __restrict__ first = L + (slows > 0 && fasts > 0 ? slow0 * ldl + fast0 : 0);
+    const TL* __restrict__ p = first + ((int64_t)s0 * ldl + fast);
+    const int64_t step = (int64_t)ds * ldl;
+#pragma unroll
+    for (int q = 0; q < kEach; ++q) {
+      const int slow = s0 + q * ds;
+      v[q] = *(slow >= lo && slow < hi ? p + q * step : first);
+    }
+  }
+  auto value = [&](int q) {
+    const int slow = s0 + q * ds;
+    const double x = slow < slows && fast < fasts ? static_cast<double>(v[q]) : 0.0;
+    return diagonal && slow == fast && (unit || slow >= slows) ? 1.0 : x;
+  };
+  // tile row / column of slow index q, and the index inside it
+  auto tile_of = [&](int q) { return TS ? q * (kInvThreads / kInvRows) / 16 : (s0 + q * ds) >> 4; };
+  auto in_tile = [&](int q) {
+    return TS ? s0 + q * (kInvThreads / kInvRows) % 16 : (s0 + q * ds) & 15;
+  };
+  if (!diagonal && !upper) {
+#pragma unroll
+    for (int q = 0; q < kEach; ++q) out[((int64_t)s0 * n0 + fast) + q * (ds * n0)] = value(q);
+    return;
+  }
+  if (!diagonal) {
+    // a transposed square goes through LDS, 64 of its columns at a time: it
+    // came in along its columns and leaves along its rows (ts = kInvRows)
+    constexpr int kHalf = kInvRows / 2, kLd = kHalf + 1;
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int q = 0; q < kEach; ++q)
+        if (q / (kEach / 2) == h) S[fast * kLd + s0 + q * ds - h * kHalf] = value(q);
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < kEach / 2; ++e) {
+        const int x = e * kInvThreads + tid;
+        out[(int64_t)(x / kHalf) * n0 + h * kHalf + x % kHalf] = S[x / kHalf * kLd + x % kHalf];
+      }
+      __syncthreads();
+    }
+    return;
+  }
+  const int ntile = (ts + 15) / 16;
+  if (ts < 16) {                        // a part of one tile: identity around it
+    if (tid < 256) S[(tid >> 4) * kTld + (tid & 15)] = (tid >> 4) == (tid & 15) ? 1.0 : 0.0;
+    __syncthreads();
+  }
+  const int ft = fast >> 4, fr = fast & 15;
+  if (upper) {                          // column `slow` of row `fast`
+    double* row = Map::at(S, ft, 0) + fr * kTld;
+#pragma unroll
+    for (int q = 0; q < kEach; ++q) {
+      const int slow = s0 + q * ds;
+      if (slow <= fast) row[tile_of(q) * kTile + in_tile(q)] = value(q);
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < kEach; ++q) {
+      const int slow = s0 + q * ds;
+      if (slow < ts && fast <= slow) Map::at(S, tile_of(q), ft)[in_tile(q) * kTld + fr] = value(q);
+    }
   }
   __syncthreads();
-  double x[64];
-  const double* L0 = &Ls[0][0];
+  const int wave = tid >> 6;
+  if (wave < ntile) invert_tile<false, false>(Map::at(S, wave, wave));
+  __syncthreads();
+  combine<Map, kInvNt, false, false>(S, ntile);
+  double* __restrict__ o = out + ((int64_t)s0 * n0 + fast);
 #pragma unroll
-  for (int i = 0; i < 64; ++i) {
-    double s4[4] = {0.0, 0.0, 0.0, 0.0};
-    // Row i is read in groups of 16 entries, each group only after the
-    // previous one is in use (and row i only after x[i-1] exists): the
-    // column of x already takes 128 registers, and reading the whole
-    // triangle ahead would spill.  The empty asm statements only make an
-    // offset depend on an earlier result.
-    int off = i * 64;
-    if (i > 0) asm volatile("" : "+v"(off) : "v"(x[i - 1]));
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      if (16 * g >= i) break;
-      int goff = off + 16 * g;
-      if (g > 0) asm volatile("" : "+v"(goff) : "v"(s4[3]));
-      const double* Lr = L0 + goff;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int p = 16 * g + e;
-        if (p < i) s4[p & 3] = fma(Lr[e], x[p], s4[p & 3]);
-      }
-    }
-    const double s = (s4[0] + s4[1]) + (s4[2] + s4[3]);
-    x[i] = ((i == t ? 1.0 : 0.0) - s) / Ls[i][i];
+  for (int q = 0; q < kEach; ++q) {
+    const int i = s0 + q * ds;
+    const double x = Map::at(S, tile_of(q), min(ft, tile_of(q)))[in_tile(q) * kTld + fr];
+    if (i < ts) o[q * (ds * n0)] = fast <= i ? x : 0.0;
   }
-#pragma unroll
-  for (int i = 0; i < 64; ++i)
-    if (i < nb && t < nb && t <= i) P[(int64_t)i * n0 + t] = x[i];
 }
 
-__global__ __launch_bounds__(256) void zero_upper_kernel(double* __restrict__ Linv, int64_t n0) {
-  // one row of one packed block per workgroup: its columns past the diagonal
-  const int64_t row = blockIdx.x;
-  const int64_t i = row % n0;
+// The last pass over the packed blocks: zeros above the diagonal (Alg.
+// RecTriInv's products used that space), the binary32 copy if one is wanted,
+// and the check of L's diagonal.  One row of one block per workgroup.
+template <typename TL>
+__global__ __launch_bounds__(256) void block_finish_kernel(const TL* __restrict__ L, int64_t ldl,
+                                                           int64_t n, int64_t n0,
+                                                           double* __restrict__ Linv,
+                                                           float* __restrict__ Linv32,
+                                                           unsigned long long* bad) {
+  const int64_t row = blockIdx.x, i = row % n0;
   double* __restrict__ out = Linv + row * n0;
-  for (int64_t j = i + 1 + threadIdx.x; j < n0; j += blockDim.x) out[j] = 0.0;
+  if (threadIdx.x == 0 && bad && row < n) {
+    const double d = static_cast<double>(L[row * ldl + row]);
+    if (!(d != 0.0) || !isfinite(d)) atomicMin(bad, (unsigned long long)row);
+  }
+  if (Linv32) {
+    float* __restrict__ o32 = Linv32 + row * n0;
+    for (int64_t j = threadIdx.x; j < n0; j += blockDim.x) {
+      o32[j] = j <= i ? static_cast<float>(out[j]) : 0.0f;
+      if (j > i) out[j] = 0.0;
+    }
+  } else {
+    for (int64_t j = i + 1 + threadIdx.x; j < n0; j += blockDim.x) out[j] = 0.0;
+  }
 }
 
 template <typename TI, typename TO>
@@ -397,30 +469,41 @@ __global__ __launch_bounds__(256) void reduce_final(const double* __restrict__ p
 }  // namespace
 
 template <typename TL>
-hipError_t launch_extract_diag(const TL* L, int64_t ldl, int64_t n, int64_t n0, int64_t m,
-                               double* Linv, unsigned long long* bad, hipStream_t s, bool upper) {
+hipError_t launch_block_inverse(const TL* L, int64_t ldl, int64_t n, int64_t n0, int64_t m,
+                                double* Linv, unsigned long long* bad, bool upper, bool unit,
+                                hipStream_t s) {
   if (m <= 0) return hipSuccess;
-  extract_diag_kernel<TL><<<(unsigned)(m * n0), row_threads(n0), 0, s>>>(L, ldl, n, n0, Linv, bad,
-                                                                         upper);
+  const int ts = (int)std::min<int64_t>(n0, kInvRows);
+  const int64_t nt = n0 / ts;
+  const unsigned grid = (unsigned)(m * nt * (nt + 1) / 2);
+  if (ts == kInvRows)
+    block_inverse_kernel<TL, kInvRows><<<grid, kInvThreads, 0, s>>>(L, ldl, n, n0, ts, m, Linv, bad,
+                                                                    upper, unit);
+  else
+    block_inverse_kernel<TL, 0><<<grid, kInvThreads, 0, s>>>(L, ldl, n, n0, ts, m, Linv, bad, upper,
+                                                             unit);
   return hipGetLastError();
 }
-template hipError_t launch_extract_diag<double>(const double*, int64_t, int64_t, int64_t, int64_t,
-                                                double*, unsigned long long*, hipStream_t, bool);
-template hipError_t launch_extract_diag<float>(const float*, int64_t, int64_t, int64_t, int64_t,
-                                               double*, unsigned long long*, hipStream_t, bool);
+template hipError_t launch_block_inverse<double>(const double*, int64_t, int64_t, int64_t, int64_t,
+                                                 double*, unsigned long long*, bool, bool,
+                                                 hipStream_t);
+template hipError_t launch_block_inverse<float>(const float*, int64_t, int64_t, int64_t, int64_t,
+                                                double*, unsigned long long*, bool, bool,
+                                                hipStream_t);
 
-hipError_t launch_trtri_leaf(double* Linv, int64_t n0, int64_t m, int64_t nb, hipStream_t s) {
+template <typename TL>
+hipError_t launch_block_finish(const TL* L, int64_t ldl, int64_t n, int64_t n0, int64_t m,
+                               double* Linv, float* Linv32, unsigned long long* bad,
+                               hipStream_t s) {
   if (m <= 0) return hipSuccess;
-  const int64_t lpb = n0 / nb;
-  trtri_leaf_kernel<<<(unsigned)(m * lpb), 64, 0, s>>>(Linv, n0, nb, lpb);
+  block_finish_kernel<TL><<<(unsigned)(m * n0), row_threads(n0), 0, s>>>(L, ldl, n, n0, Linv,
+                                                                         Linv32, bad);
   return hipGetLastError();
 }
-
-hipError_t launch_zero_upper(double* Linv, int64_t n0, int64_t m, hipStream_t s) {
-  if (m <= 0) return hipSuccess;
-  zero_upper_kernel<<<(unsigned)(m * n0), row_threads(n0), 0, s>>>(Linv, n0);
-  return hipGetLastError();
-}
+template hipError_t launch_block_finish<double>(const double*, int64_t, int64_t, int64_t, int64_t,
+                                                double*, float*, unsigned long long*, hipStream_t);
+template hipError_t launch_block_finish<float>(const float*, int64_t, int64_t, int64_t, int64_t,
+                                               double*, float*, unsigned long long*, hipStream_t);
 
 template <typename TI, typename TO>
 hipError_t launch_convert(const TI* in, TO* out, int64_t count, hipStream_t s) {

@@ -5,23 +5,30 @@
 
 namespace trsm {
 
-// Copy the m diagonal n0 x n0 blocks of L (lower part, zeros above) into the
-// packed binary64 buffer Linv; positions past row/column n get the identity.
-// Records min(row) of any zero / non-finite diagonal entry in *bad.  With
-// `upper`, L is an upper-triangular U and the blocks copied are U_bb^T (the
-// lower triangles of the transposed diagonal blocks; U below its diagonal is
-// not read).
+// Rows of the squares inverted in LDS.
+constexpr int kInvRows = 128;
+
+// The m diagonal n0 x n0 blocks of L (lower part) in the packed binary64 buffer
+// Linv with every diagonal square of min(n0, kInvRows) rows inverted (zeros
+// above its diagonal) and the squares below copied; positions past row/column n
+// hold the identity.  With `upper`, L is an upper-triangular U and the blocks
+// are U_bb^T (U below its diagonal is not read); with `unit`, L's diagonal is
+// taken as one.  *bad (unless null) becomes all ones.
 template <typename TL>
-hipError_t launch_extract_diag(const TL* L, int64_t ldl, int64_t n, int64_t n0, int64_t m,
-                               double* Linv, unsigned long long* bad, hipStream_t s,
-                               bool upper = false);
+hipError_t launch_block_inverse(const TL* L, int64_t ldl, int64_t n, int64_t n0, int64_t m,
+                                double* Linv, unsigned long long* bad, bool upper, bool unit,
+                                hipStream_t s);
 
-// Invert, in place, every nb x nb diagonal leaf of every packed block
-// (nb <= 64): column-oriented substitution on the identity in LDS.
-hipError_t launch_trtri_leaf(double* Linv, int64_t n0, int64_t m, int64_t nb, hipStream_t s);
+// The levels of Alg. RecTriInv above those squares (defined in trsm.hip).
+hipError_t rec_tri_inv_levels(double* Linv, int64_t n0, int64_t m, hipStream_t s);
 
-// Zero the strict upper triangle of every packed block.
-hipError_t launch_zero_upper(double* Linv, int64_t n0, int64_t m, hipStream_t s);
+// After the whole blocks are inverted: zeros above their diagonals, the binary32
+// copy Linv32 (unless null), and min(row) of the zero / non-finite diagonal
+// entries of L in *bad (unless null).
+template <typename TL>
+hipError_t launch_block_finish(const TL* L, int64_t ldl, int64_t n, int64_t n0, int64_t m,
+                               double* Linv, float* Linv32, unsigned long long* bad,
+                               hipStream_t s);
 
 // out[i] = (TO) in[i]
 template <typename TI, typename TO>

@@ -14,7 +14,7 @@
 //       A(c:c+w, c+w:c0+s) = Lp^{-1} A(c:c+w, c+w:c0+s)  (unit lower, w x w)
 //       A(c+w:n, c+w:c0+s) -= A(c+w:n, c:c+w) A(c:c+w, c+w:c0+s)
 //     Linv_jj = L_jj^{-1}  (Alg. Diagonal-Inverter + RecTriInv on the unit
-//       lower diagonal block, through trsm_invert_diag)
+//       lower diagonal block)
 //     U(S_j, T_j) = Linv_jj A(S_j, T_j)         (the panel solve: one product)
 //     A(T_j, T_j) -= L(T_j, S_j) U(S_j, T_j)
 //
@@ -514,17 +514,6 @@ __global__ __launch_bounds__(kSwapCols) void swap_rows_kernel(double* __restrict
   }
 }
 
-// W (nb x nb) = the unit lower triangle of the s x s block D: strictly lower
-// part from D, ones on the diagonal, zeros above, identity past s.
-__global__ __launch_bounds__(256) void unit_lower_copy_kernel(const double* __restrict__ D,
-                                                              int64_t ldd, int64_t s,
-                                                              double* __restrict__ W, int64_t nb) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= nb * nb) return;
-  const int64_t i = e / nb, c = e % nb;
-  W[e] = (c < i) ? ((i < s) ? D[i * ldd + c] : 0.0) : (c == i ? 1.0 : 0.0);
-}
-
 #define PIV_HIP(...)                                              \
   do {                                                            \
     hipError_t e_ = (__VA_ARGS__);                                \
@@ -539,7 +528,7 @@ __global__ __launch_bounds__(256) void unit_lower_copy_kernel(const double* __re
 
 struct Layout {
   int64_t nb, m;
-  size_t words, slots, w, winv, wu, split, total, inv_bytes, plan_linv;
+  size_t words, slots, wu, split, total, inv_bytes;
 };
 
 int64_t default_nb(int64_t n) { return n <= 4096 ? 256 : 512; }
@@ -558,20 +547,11 @@ trsm_status layout_for(int64_t n, int64_t nb, Layout* L) {
   nb = std::max<int64_t>(kPw, std::min(nb, pow2_at_least(n)));
   L->nb = nb;
   L->m = (n + nb - 1) / nb;
-  trsm_plan_t plan = nullptr;
-  PIV_TRY(trsm_plan(nb, 1, TRSM_F64, nb, 0, &plan));
-  trsm_plan_info pi;
-  const trsm_status st = trsm_plan_get_info(plan, &pi);
-  trsm_plan_destroy(plan);
-  if (st != TRSM_OK) return st;
-  L->plan_linv = pi.linv_bytes;
   L->words = al(sizeof(Words));
   L->slots = al((size_t)2 * kMaxGroups * kSlotWords * 8) + al(sizeof(Moves));
-  L->w = al((size_t)nb * nb * 8);
-  L->winv = al(pi.linv_bytes);
   L->wu = al((size_t)nb * std::max<int64_t>(n - nb, 1) * 8);
   L->split = kSplitBytes;
-  L->total = L->words + L->slots + L->w + L->winv + L->wu + L->split;
+  L->total = L->words + L->slots + L->wu + L->split;
   L->inv_bytes = (size_t)L->m * nb * nb * 8;
   return TRSM_OK;
 }
@@ -628,8 +608,6 @@ trsm_status factor(int64_t n, double* A, int64_t lda, const Layout& L, int64_t* 
   unsigned long long* slots = (unsigned long long*)q;
   Moves* mv = (Moves*)(q + al((size_t)2 * kMaxGroups * kSlotWords * 8));
   q += L.slots;
-  double* W = (double*)q;      q += L.w;
-  double* Winv = (double*)q;   q += L.winv;
   double* WU = (double*)q;     q += L.wu;
   void* split = q;
   // words: bad = all ones, err = 0; no slot carries a step number of this call
@@ -637,8 +615,6 @@ trsm_status factor(int64_t n, double* A, int64_t lda, const Layout& L, int64_t* 
   PIV_HIP(launch_fill_u32((unsigned*)words + 2, 2, 0u, s));
   if (n > kThreads * kMaxRpt)
     PIV_HIP(launch_fill_u32((unsigned*)slots, (int64_t)4 * kMaxGroups * kSlotWords, 0u, s));
-  trsm_plan_t plan = nullptr;
-  PIV_TRY(trsm_plan(nb, 1, TRSM_F64, nb, 0, &plan));
   trsm_status st = TRSM_OK;
   for (int64_t j = 0; j < L.m && st == TRSM_OK; ++j) {
     const int64_t c0 = j * nb, sb = std::min(nb, n - c0), e0 = c0 + sb;
@@ -667,22 +643,17 @@ trsm_status factor(int64_t n, double* A, int64_t lda, const Layout& L, int64_t* 
     }
     // Linv_jj: the unit lower diagonal block, inverted by Alg.
     // Diagonal-Inverter + RecTriInv (one block of nb rows)
-    if (e == hipSuccess) {
-      unit_lower_copy_kernel<<<(unsigned)ceil_div(nb * nb, 256), 256, 0, s>>>(
-          A + c0 * lda + c0, lda, sb, W, nb);
-      e = hipGetLastError();
-    }
-    if (e != hipSuccess) {
-      st = (trsm_status)note_hip_error(e);
-      break;
-    }
-    st = trsm_invert_diag(plan, W, nb, Winv, s);
-    if (st != TRSM_OK) break;
-    e = launch_copy2d<double, double>(Winv, nb, Linv + j * nb * nb, nb, nb, nb, 1.0, s);
+    double* Lj = Linv + j * nb * nb;
+    if (e == hipSuccess)
+      e = launch_block_inverse<double>(A + c0 * lda + c0, lda, sb, nb, 1, Lj, nullptr, false, true,
+                                       s);
+    if (e == hipSuccess) e = rec_tri_inv_levels(Lj, nb, 1, s);
+    if (e == hipSuccess && nb > kInvRows)
+      e = launch_block_finish<double>(nullptr, 0, 0, nb, 1, Lj, nullptr, nullptr, s);
     const int64_t t = n - e0;
     if (e == hipSuccess && t > 0) {
       // U(S_j, T_j) = Linv_jj A(S_j, T_j), then the trailing update
-      e = prod(Linv + j * nb * nb, nb, A + c0 * lda + e0, lda, WU, t, sb, t, sb, 1.0, false,
+      e = prod(Lj, nb, A + c0 * lda + e0, lda, WU, t, sb, t, sb, 1.0, false,
                G_A_LOWER | G_A_ZERO_UPPER, split, kSplitBytes, s);
       if (e == hipSuccess) e = launch_copy2d<double, double>(WU, t, A + c0 * lda + e0, lda, sb, t,
                                                              1.0, s);
@@ -692,7 +663,6 @@ trsm_status factor(int64_t n, double* A, int64_t lda, const Layout& L, int64_t* 
     }
     if (e != hipSuccess) st = (trsm_status)note_hip_error(e);
   }
-  trsm_plan_destroy(plan);
   return st;
 }
 

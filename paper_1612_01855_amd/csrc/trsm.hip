@@ -323,17 +323,15 @@ bool ranges_overlap(const void* a, size_t abytes, const void* b, size_t bbytes) 
 // ---------------------------------------------------------------------------
 // A1: Alg. Diagonal-Inverter / Alg. RecTriInv.
 // ---------------------------------------------------------------------------
-namespace {
-
-// All levels of the recursive inversion, batched over every pair of every
-// block.  At level h the pair [[A11, 0], [A21, A22]] (2h x 2h, A11 and A22
+// The levels of the recursive inversion above the squares inverted in LDS,
+// batched over every pair of every block.  At level h the pair [[A11, 0], [A21, A22]] (2h x 2h, A11 and A22
 // already inverted) is completed with
 //     T   = A22^{-1} A21          (stored in the pair's unused upper-right)
 //     A21 = -T A11^{-1}
 // which is Alg. RecTriInv's combine, -(Linv22 L21) Linv11, in the paper's
 // association order.
-hipError_t rec_tri_inv_levels(double* Linv, int64_t n0, int64_t m, int64_t nb, hipStream_t s) {
-  for (int64_t h = nb; h < n0; h *= 2) {
+hipError_t trsm::rec_tri_inv_levels(double* Linv, int64_t n0, int64_t m, hipStream_t s) {
+  for (int64_t h = kInvRows; h < n0; h *= 2) {
     const int64_t ppb = n0 / (2 * h);  // pairs per block
     auto p = gemm_params<double, double, double, float>();
     p.M = p.N = p.K = (int)h;
@@ -357,8 +355,6 @@ hipError_t rec_tri_inv_levels(double* Linv, int64_t n0, int64_t m, int64_t nb, h
   }
   return hipSuccess;
 }
-
-}  // namespace
 
 // ---------------------------------------------------------------------------
 // A2/A3: the blocked sweep of Alg. It-Inv-TRSM, right-looking.
@@ -1086,21 +1082,20 @@ trsm_status trsm_invert_diag(trsm_plan_t P, const void* L, int64_t ldl, void* Li
   const bool large = P->flags & TRSM_FLAG_LARGE_TILES;
   TilePolicyScope tile_scope(large);
   SplitScope split_scope(nullptr, 0);
-  TRSM_HIP(launch_fill_u32((unsigned*)bad, 2, 0xFFFFFFFFu, s));
   // an upper plan inverts the transposed blocks U_ii^T (lower) and
   // transposes the inverses back below
   const bool upper = P->flags & TRSM_FLAG_UPPER;
-  if (P->prec == TRSM_F32)
-    TRSM_HIP(launch_extract_diag<float>((const float*)L, ldl, n, n0, m, L64, bad, s, upper));
-  else
-    TRSM_HIP(launch_extract_diag<double>((const double*)L, ldl, n, n0, m, L64, bad, s, upper));
-  TRSM_HIP(launch_trtri_leaf(L64, n0, m, P->leaf, s));
-  if (P->leaf < n0) {
-    TRSM_HIP(rec_tri_inv_levels(L64, n0, m, P->leaf, s));
-    TRSM_HIP(launch_zero_upper(L64, n0, m, s));
+  float* L32 = P->prec != TRSM_F64 ? (float*)(base + P->off_linv32) : nullptr;
+  if (P->prec == TRSM_F32) {
+    TRSM_HIP(launch_block_inverse<float>((const float*)L, ldl, n, n0, m, L64, bad, upper, false, s));
+    TRSM_HIP(rec_tri_inv_levels(L64, n0, m, s));
+    TRSM_HIP(launch_block_finish<float>((const float*)L, ldl, n, n0, m, L64, L32, bad, s));
+  } else {
+    TRSM_HIP(launch_block_inverse<double>((const double*)L, ldl, n, n0, m, L64, bad, upper, false,
+                                          s));
+    TRSM_HIP(rec_tri_inv_levels(L64, n0, m, s));
+    TRSM_HIP(launch_block_finish<double>((const double*)L, ldl, n, n0, m, L64, L32, bad, s));
   }
-  if (P->prec != TRSM_F64)
-    TRSM_HIP((launch_convert<double, float>(L64, (float*)(base + P->off_linv32), m * n0 * n0, s)));
   if (P->flags & TRSM_FLAG_TRANSPOSE) {
     // U = L^T (zeros below the diagonal) and Uinv_ii = Linv_ii^T
     if (P->prec == TRSM_F32) {
