@@ -460,6 +460,15 @@ constexpr int kBM = 128, kBN = 128;
 // work of a 128 x 128 tile on padding.  The k order of every element is the
 // same as with the wide tiles, so the bits are too.
 constexpr int kNarrowN = 32;
+// Tile shapes of grouped products.  64 x 64 tiles for products of more columns
+// that have fewer than kWideFrom 128 x 128 workgroups: a 128 x 128 tile's chunk takes
+// 2.2 us (one workgroup on a compute unit) against 0.7, so the tall factors' tiles
+// set a launch's time, and operands that are not 16-byte aligned (their copies of
+// a large tile would exceed the counter of outstanding copies).
+enum { kNarrow, kMid, kWide, kShapes };
+constexpr int kMidTile = 64;
+constexpr int kWideFrom = 256;
+constexpr int kMidSplitBelow = 128;
 
 // Waits of the persistent sweep give up (and set the error word) after this
 // many polls of about a microsecond; by construction a wait always ends long
@@ -580,6 +589,34 @@ hipError_t launch_persist(const void* items, const void* tasks, int ntasks, unsi
   return hipGetLastError();
 }
 
+template <typename T, int BM, int BN, int WGM, int WGN, int MODE>
+void launch_grouped_as(const GemmParams<T, T, T, float>* e, const int* start, int count, dim3 grid,
+                       hipStream_t s) {
+  gemm_grouped_kernel<T, T, T, float, BM, BN, WGM, WGN, false, MODE><<<grid, 256, 0, s>>>(e, start,
+                                                                                         count);
+}
+
+// One grouped launch of products that share a tile shape and a mode.
+template <typename T>
+void launch_grouped(const GemmParams<T, T, T, float>* e, const int* start, int count, int shape,
+                    int mode, dim3 grid, hipStream_t s) {
+  auto pick = [&](auto by16, auto by16a, auto by4) {
+    (mode == kDma16 ? by16 : mode == kDma16A ? by16a : by4)(e, start, count, grid, s);
+  };
+  if (shape == kNarrow)
+    pick(launch_grouped_as<T, kBM, kNarrowN, 4, 1, kDma16>,
+         launch_grouped_as<T, kBM, kNarrowN, 4, 1, kDma16A>,
+         launch_grouped_as<T, kBM, kNarrowN, 4, 1, kDma4>);
+  else if (shape == kMid)
+    pick(launch_grouped_as<T, kMidTile, kMidTile, 2, 2, kDma16>,
+         launch_grouped_as<T, kMidTile, kMidTile, 2, 2, kDma16A>,
+         launch_grouped_as<T, kMidTile, kMidTile, 2, 2, kDma4>);
+  else if (mode == kDma16)
+    launch_grouped_as<T, kBM, kBN, 2, 2, kDma16>(e, start, count, grid, s);
+  else
+    launch_grouped_as<T, kBM, kBN, 2, 2, kStaged>(e, start, count, grid, s);
+}
+
 }  // namespace
 
 void LaunchList::clear() {
@@ -596,9 +633,9 @@ size_t LaunchList::append(const T* data, size_t n) {
 }
 
 namespace {
-// Split of one grouped product (see SweepItem::part): products with at most
-// half a round of 128 x 128 workgroups cut K into up to kSplitMax slices of
-// at least kSplitMinChunks chunks each, as far as the scratch holds them.
+// Split of one grouped product (see SweepItem::part): products with few
+// workgroups cut K into up to kSplitMax slices of at least kSplitMinChunks
+// chunks each, as far as the scratch holds them.
 template <typename T>
 int grouped_ksplit(const GemmParams<T, T, T, float>& p) {
   if (!p.part) return 1;
@@ -608,8 +645,12 @@ int grouped_ksplit(const GemmParams<T, T, T, float>& p) {
 
 int grouped_split_slices(int M, int N, int K, uint32_t flags, int64_t part_bytes, int elem) {
   if (M <= 0 || N <= 0) return 1;
-  const int64_t tiles = gemm_wgs(M, N, K, flags, kBM, kBN);
-  if (2 * tiles > kSplitTarget) return 1;
+  // 128 x 32 tiles: up to one round of two workgroups per compute unit; 64 x 64
+  // tiles (a quarter of the chain per chunk): only below half a workgroup per unit
+  const bool narrow = N <= kNarrowN;
+  const int64_t tiles = narrow ? gemm_wgs(M, N, K, flags, kBM, kBN)
+                               : gemm_wgs(M, N, K, flags, kMidTile, kMidTile);
+  if (tiles > (narrow ? kSplitTarget / 2 : kMidSplitBelow)) return 1;
   const int64_t nck = (K + 128 / elem - 1) / (128 / elem);   // chunks of 128 bytes
   int64_t S = std::min<int64_t>(kSplitTarget / tiles, nck / kSplitMinChunks);
   S = std::min<int64_t>(S, kSplitMax);
@@ -621,33 +662,42 @@ template <typename P>
 void LaunchList::add_gemm(int kind, int split_kind, std::vector<P> entries) {
   if (entries.empty()) return;
   using T = typename std::remove_const<typename std::remove_pointer<decltype(P::A)>::type>::type;
-  // sub-launches: aligned narrow, aligned wide, unaligned (wide tiles)
-  std::vector<P> sub[3];
+  // sub-launches by tile shape and by how the operands reach LDS; both follow from
+  // the entry alone, so its tiles and sums do not depend on the others
+  std::vector<P> sub[kShapes][kDma16 + 1];
   std::vector<P> split;
   for (P& e : entries) {
     e.ksplit = grouped_ksplit<T>(e);
     if (e.ksplit > 1) split.push_back(e);
-    const bool al = gemm_aligned<T, kBM, kBN, false>(e);
-    sub[!al ? 2 : (e.N <= kNarrowN ? 0 : 1)].push_back(e);
-  }
-  for (int v = 0; v < 3; ++v) {
-    if (sub[v].empty()) continue;
-    Phase ph{};
-    ph.kind = kind;
-    ph.count = (int)sub[v].size();
-    ph.aligned = v < 2;
-    ph.narrow = v == 0;
-    const int bn = ph.narrow ? kNarrowN : kBN;
-    std::vector<int> st(sub[v].size() + 1, 0);
-    for (size_t i = 0; i < sub[v].size(); ++i) {
-      const P& e = sub[v][i];
-      st[i + 1] = st[i] + gemm_wgs(e.M, e.N, e.K, e.flags, kBM, bn) * e.ksplit;
+    const int mode = gemm_mode<T, kBM, kBN, false>(e);
+    int shape = kWide;
+    if (mode != kStaged) {
+      if (e.N <= kNarrowN) shape = kNarrow;
+      else if (mode != kDma16 ||
+               gemm_wgs(e.M, e.N, e.K, e.flags, kBM, kBN) * e.ksplit < kWideFrom)
+        shape = kMid;
     }
-    ph.total = st.back();
-    ph.entries_off = append(sub[v].data(), sub[v].size());
-    ph.start_off = append(st.data(), st.size());
-    if (ph.total > 0) phases_.push_back(ph);
+    sub[shape][mode].push_back(e);
   }
+  for (int shape = 0; shape < kShapes; ++shape)
+    for (int mode = 0; mode <= kDma16; ++mode) {
+      const std::vector<P>& v = sub[shape][mode];
+      if (v.empty()) continue;
+      Phase ph{};
+      ph.kind = kind;
+      ph.count = (int)v.size();
+      ph.shape = shape;
+      ph.mode = mode;
+      const int bm = shape == kMid ? kMidTile : kBM;
+      const int bn = shape == kMid ? kMidTile : shape == kNarrow ? kNarrowN : kBN;
+      std::vector<int> st(v.size() + 1, 0);
+      for (size_t i = 0; i < v.size(); ++i)
+        st[i + 1] = st[i] + gemm_wgs(v[i].M, v[i].N, v[i].K, v[i].flags, bm, bn) * v[i].ksplit;
+      ph.total = st.back();
+      ph.entries_off = append(v.data(), v.size());
+      ph.start_off = append(st.data(), st.size());
+      if (ph.total > 0) phases_.push_back(ph);
+    }
   if (split.empty()) return;
   Phase fin{};
   fin.kind = split_kind;
@@ -753,27 +803,11 @@ hipError_t LaunchList::run(const void* dev, hipStream_t s) const {
     const int* st = reinterpret_cast<const int*>(base + ph.start_off);
     dim3 grid((unsigned)ph.total);
     if (ph.kind == PH_GEMM_F64) {
-      const GemmP64* e = reinterpret_cast<const GemmP64*>(base + ph.entries_off);
-      if (ph.narrow)
-        gemm_grouped_kernel<double, double, double, float, kBM, kNarrowN, 4, 1, false, true>
-            <<<grid, 256, 0, s>>>(e, st, ph.count);
-      else if (ph.aligned)
-        gemm_grouped_kernel<double, double, double, float, kBM, kBN, 2, 2, false, true>
-            <<<grid, 256, 0, s>>>(e, st, ph.count);
-      else
-        gemm_grouped_kernel<double, double, double, float, kBM, kBN, 2, 2, false, false>
-            <<<grid, 256, 0, s>>>(e, st, ph.count);
+      launch_grouped<double>(reinterpret_cast<const GemmP64*>(base + ph.entries_off), st, ph.count,
+                             ph.shape, ph.mode, grid, s);
     } else if (ph.kind == PH_GEMM_F32) {
-      const GemmP32* e = reinterpret_cast<const GemmP32*>(base + ph.entries_off);
-      if (ph.narrow)
-        gemm_grouped_kernel<float, float, float, float, kBM, kNarrowN, 4, 1, false, true>
-            <<<grid, 256, 0, s>>>(e, st, ph.count);
-      else if (ph.aligned)
-        gemm_grouped_kernel<float, float, float, float, kBM, kBN, 2, 2, false, true>
-            <<<grid, 256, 0, s>>>(e, st, ph.count);
-      else
-        gemm_grouped_kernel<float, float, float, float, kBM, kBN, 2, 2, false, false>
-            <<<grid, 256, 0, s>>>(e, st, ph.count);
+      launch_grouped<float>(reinterpret_cast<const GemmP32*>(base + ph.entries_off), st, ph.count,
+                            ph.shape, ph.mode, grid, s);
     } else if (ph.kind == PH_SPLIT_F64) {
       const GemmP64* e = reinterpret_cast<const GemmP64*>(base + ph.entries_off);
       grouped_split_finish<double><<<grid, 256, 0, s>>>(e, st, ph.count);

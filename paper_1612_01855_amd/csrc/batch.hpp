@@ -157,8 +157,8 @@ class LaunchList {
     size_t start_off;    // byte offset of the int prefix array (n + 1 values); tasks (persistent)
     int count;
     int total;           // workgroups
-    bool aligned;
-    bool narrow = false;            // products of at most kNarrowN columns: 128 x 32 tiles
+    bool aligned;                   // persistent sweep
+    int shape = 0, mode = 0;        // grouped products: tile shape and GemmMode
     unsigned* counters = nullptr;   // persistent: counters, queue head, error word
     int ncounters = 0;
     int ntasks = 0;

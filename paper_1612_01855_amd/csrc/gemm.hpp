@@ -21,10 +21,10 @@
 //
 // Work decomposition: a workgroup of WGM x WGN waves owns a BM x BN tile;
 // each wave owns (BM/WGM) x (BN/WGN) made of 16x16 MFMA tiles.  K advances in
-// chunks of 128 bytes with two LDS stages and one barrier per chunk.  Aligned
-// binary64/binary32 products copy their operands from HBM directly into LDS
-// (buffer loads with the LDS modifier, no register staging); the general
-// path stages them through registers.  Square lower-triangular products are
+// chunks of 128 bytes with two LDS stages and one barrier per chunk.
+// Binary64/binary32 products copy their operands from HBM directly into LDS
+// (buffer loads with the LDS modifier, no register staging), other types stage
+// them through registers.  Square lower-triangular products are
 // folded so that every workgroup gets equal work.  Tiles are visited in groups of GROUP_M row
 // tiles (column-major inside a group) so that concurrently running
 // workgroups share A and B panels in L2.  The hardware deals consecutive
@@ -41,6 +41,9 @@
 #include <type_traits>
 
 namespace trsm {
+
+// How a product's operands reach LDS (gemm_mode).
+enum GemmMode { kStaged, kDma4, kDma16A, kDma16 };
 
 enum GemmFlags : uint32_t {
   G_A_LOWER = 1u,
@@ -340,8 +343,13 @@ constexpr int kWaitAll = 0x7 << 4;
 
 // Matrix-core tile with operands copied from HBM straight into LDS by
 // buffer loads (no register staging), two LDS stages, one barrier per chunk.
-// For one-k-per-lane instructions (binary64, binary32) and 16-byte aligned
-// operands.  LDS layout per stage:
+// For one-k-per-lane instructions (binary64, binary32).  A16 / B16: the operand's
+// rows are 16-byte aligned and are copied 16 bytes a lane; otherwise 4 bytes a
+// lane into the same layout (element alignment is enough, and nothing past a row's
+// end is read), four times as many copies but still without registers or a wait
+// (6000 x 6000 x 1024 in 64 x 64 tiles: binary64 1372 us, staged through registers
+// 1651 and in 128 x 128 tiles 1606; binary32 726, 1086 and 1042).  LDS layout
+// per stage:
 //  * A: BM rows of 128 bytes (BK elements), the eight 16-byte pieces of row r
 //    stored XOR-swizzled (piece d at position d ^ (r & 7)), so that the 16
 //    rows a fragment read touches fall in different banks;
@@ -360,7 +368,7 @@ constexpr int kWaitAll = 0x7 << 4;
 // Triangular masks are applied to the fragments, only in chunks that cross
 // the diagonal.
 template <typename TIn, typename TCin, typename TCout, typename TC2, int BM, int BN, int WGM,
-          int WGN, bool BKMAJOR = false>
+          int WGN, bool BKMAJOR = false, bool A16 = true, bool B16 = true>
 __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout, TC2>& p, int z,
                                               int s, const int r0, const int c0) {
   using MF = Mfma<TIn>;
@@ -421,43 +429,63 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout,
     const int k0 = kbeg + c * BK;
     const int kend = !RUNON || c < nchunks ? K : 0;
     char* base = smem + st * STAGE;
-    const __amdgpu_buffer_rsrc_t ra = make_rsrc(A + (int64_t)r0 * lda + k0);
+    // rows [row0, row0 + 8 INST NW) of a k-contiguous operand, swizzled
+    auto rows_of = [&](const TIn* P, int ld, int row0, int rows, char* dst, auto inst, auto wide) {
+      const __amdgpu_buffer_rsrc_t rs = make_rsrc(P + (int64_t)row0 * ld + k0);
 #pragma unroll
-    for (int q = 0; q < A_INST; ++q) {
-      const int rb = 8 * (wave * A_INST + q);
-      const int r = rb + (lane >> 3);
-      const int d = (lane & 7) ^ (r & 7);
-      const bool ok = (r0 + r < M) && (k0 + d * VEC < kend);
-      const int off = ok ? (r * lda + d * VEC) * ES : kBufOOB;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          ra, (__attribute__((address_space(3))) void*)(base + rb * 128), 16, off, 0, 0, 0);
-    }
-    if constexpr (BKMAJOR) {
-      const __amdgpu_buffer_rsrc_t rbt = make_rsrc(B + (int64_t)c0 * ldb + k0);
+      for (int q = 0; q < inst(); ++q) {
+        const int rb = 8 * (wave * inst() + q);
+        if constexpr (wide()) {
+          const int r = rb + (lane >> 3);
+          const int d = (lane & 7) ^ (r & 7);
+          const bool ok = (row0 + r < rows) && (k0 + d * VEC < kend);
+          const int off = ok ? (r * ld + d * VEC) * ES : kBufOOB;
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(
+              rs, (__attribute__((address_space(3))) void*)(dst + rb * 128), 16, off, 0, 0, 0);
+        } else {
 #pragma unroll
-      for (int q = 0; q < BT_INST; ++q) {
-        const int rb = 8 * (wave * BT_INST + q);
-        const int r = rb + (lane >> 3);
-        const int d = (lane & 7) ^ (r & 7);
-        const bool ok = (c0 + r < N) && (k0 + d * VEC < kend);
-        const int off = ok ? (r * ldb + d * VEC) * ES : kBufOOB;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            rbt, (__attribute__((address_space(3))) void*)(base + A_BYTES + rb * 128), 16, off, 0,
-            0, 0);
+          for (int w = 0; w < 4; ++w) {   // two rows a copy
+            const int r = rb + 2 * w + (lane >> 5);
+            const int byte = ((((lane & 31) >> 2) ^ (r & 7)) << 4) + ((lane & 3) << 2);
+            const bool ok = (row0 + r < rows) && (k0 + byte / ES < kend);
+            const int off = ok ? r * ld * ES + byte : kBufOOB;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rs, (__attribute__((address_space(3))) void*)(dst + rb * 128 + w * 256), 4, off, 0,
+                0, 0);
+          }
+        }
       }
-      return;
-    }
-    const __amdgpu_buffer_rsrc_t rbs = make_rsrc(B + (int64_t)k0 * ldb + c0);
+    };
+    rows_of(A, lda, r0, M, base, std::integral_constant<int, A_INST>(),
+            std::integral_constant<bool, A16>());
+    if constexpr (BKMAJOR) {
+      rows_of(B, ldb, c0, N, base + A_BYTES, std::integral_constant<int, BT_INST>(),
+              std::integral_constant<bool, B16>());
+    } else {
+      const __amdgpu_buffer_rsrc_t rbs = make_rsrc(B + (int64_t)k0 * ldb + c0);
 #pragma unroll
-    for (int q = 0; q < B_INST; ++q) {
-      const int qi = wave * B_INST + q;
-      const int kr = qi * RPI + lane / (64 / RPI);
-      const int cv = (lane % (64 / RPI)) * VEC;
-      const bool ok = (k0 + kr < kend) && (c0 + cv < N);
-      const int off = ok ? (kr * ldb + cv) * ES : kBufOOB;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          rbs, (__attribute__((address_space(3))) void*)(base + A_BYTES + qi * (1024 + 16)), 16,
-          off, 0, 0, 0);
+      for (int q = 0; q < B_INST; ++q) {
+        const int qi = wave * B_INST + q;
+        char* dst = base + A_BYTES + qi * (1024 + 16);
+        if constexpr (B16) {
+          const int kr = qi * RPI + lane / (64 / RPI);
+          const int cv = (lane % (64 / RPI)) * VEC;
+          const bool ok = (k0 + kr < kend) && (c0 + cv < N);
+          const int off = ok ? (kr * ldb + cv) * ES : kBufOOB;
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(
+              rbs, (__attribute__((address_space(3))) void*)dst, 16, off, 0, 0, 0);
+        } else {
+#pragma unroll
+          for (int w = 0; w < 4; ++w) {
+            const int x = w * 256 + lane * 4;   // byte of this copy's 1 KB of rows
+            const int kr = qi * RPI + x / ROW_B, byte = x % ROW_B;
+            const bool ok = (k0 + kr < kend) && (c0 + byte / ES < N);
+            const int off = ok ? kr * ldb * ES + byte : kBufOOB;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rbs, (__attribute__((address_space(3))) void*)(dst + w * 256), 4, off, 0, 0, 0);
+          }
+        }
+      }
     }
   };
   // Fragments of half h (the lane group's h-th 16-byte piece of k) of chunk c.
@@ -495,8 +523,17 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout,
       }
     }
   };
+  // 16-byte pieces of A beside 4-byte copies of B: the last piece may reach past K
+  const int k_tail = A16 && !B16 && K % VEC ? K : INT32_MAX;
   auto mask = [&](Half& f, int c, int h) {
     const int k0 = kbeg + c * BK;
+    if (k0 + BK > k_tail) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e)
+          if (k0 + g * KL + h * VEC + e >= k_tail) f.a[i][e] = TIn(0);
+    }
     if (a_lower && k0 + BK - 1 > r0 + wm * WTM) {
 #pragma unroll
       for (int i = 0; i < TM; ++i)
@@ -522,7 +559,9 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout,
   };
 
   if (nchunks > 0) {
-    constexpr int LPC = A_INST + (BKMAJOR ? BT_INST : B_INST);   // copies per wave and chunk
+    // copies per wave and chunk
+    constexpr int LPC = A_INST * (A16 ? 1 : 4) + (BKMAJOR ? BT_INST : B_INST) * (B16 ? 1 : 4);
+    static_assert(LPC < 32, "two chunks' copies fit the counter of outstanding copies");
     Half f0, f1;
     issue(0, 0);
     if (RUNON || nchunks > 1) {
@@ -533,7 +572,7 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout,
     }
     __syncthreads();                                // ... everyone's
     fetch(f0, 0, 0);
-    const bool masked = a_lower || b_lower;
+    const bool masked = a_lower || b_lower || k_tail != INT32_MAX;
     for (int c = 0; c < nchunks; ++c) {
       // the reads go out before the MFMAs (the scheduler would sink them)
       fetch(f1, c, 1);
@@ -559,8 +598,8 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout,
                                                         gi);
 }
 
-// Register-staged tile: every operand layout and alignment (the general
-// path; bfloat16/half products with k-contiguous B, and unaligned operands).
+// Register-staged tile: bfloat16/half products with k-contiguous B, and any product
+// whose tiles span more than a buffer descriptor.
 template <typename TIn, typename TCin, typename TCout, typename TC2,
           int BM, int BN, int WGM, int WGN, bool BKMAJOR, bool ALIGNED>
 __device__ __forceinline__ void gemm_tile_staged(const GemmParams<TIn, TCin, TCout, TC2>& p,
@@ -774,19 +813,23 @@ __device__ __forceinline__ void gemm_tile_staged(const GemmParams<TIn, TCin, TCo
 // The output tiles of workgroup `bid` (of nwg) of one batch entry z: one
 // tile, or two for a folded triangular product.
 template <typename TIn, typename TCin, typename TCout, typename TC2,
-          int BM, int BN, int WGM, int WGN, bool BKMAJOR, bool ALIGNED, bool CLOWER = false,
+          int BM, int BN, int WGM, int WGN, bool BKMAJOR, int MODE, bool CLOWER = false,
           int GROUP_M = 8, bool XCD_REMAP = false>
 __device__ __forceinline__ void gemm_tile(const GemmParams<TIn, TCin, TCout, TC2>& p, int z,
                                           int s, int bid, int nwg) {
   const int ntm = (p.M + BM - 1) / BM, ntn = (p.N + BN - 1) / BN;
+  auto one = [&](int tm, int tn) {
+    if constexpr (MODE != kStaged && Mfma<TIn>::kPerLane == 1)
+      gemm_tile_dma<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, MODE != kDma4, MODE == kDma16>(
+          p, z, s, tm * BM, tn * BN);
+    else
+      gemm_tile_staged<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, MODE == kDma16>(
+          p, z, s, tm * BM, tn * BN);
+  };
   if constexpr (CLOWER) {
     int tm, tn;
     lower_tile(ntm, bid, nwg, tm, tn);
-    if constexpr (ALIGNED && Mfma<TIn>::kPerLane == 1)
-      gemm_tile_dma<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR>(p, z, s, tm * BM, tn * BN);
-    else
-      gemm_tile_staged<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, ALIGNED>(p, z, s, tm * BM,
-                                                                               tn * BN);
+    one(tm, tn);
     return;
   }
   const bool fold = tri_fold(p.M, p.K, p.flags, BM);
@@ -794,17 +837,10 @@ __device__ __forceinline__ void gemm_tile(const GemmParams<TIn, TCin, TCout, TC2
   const int rows = fold ? (ntm + 1) / 2 : ntm;
   int slot, tn;
   tile_slot<GROUP_M, XCD_REMAP>(rows, ntn, uniform, bid, nwg, slot, tn);
-  auto one = [&](int tm) {
-    if constexpr (ALIGNED && Mfma<TIn>::kPerLane == 1)
-      gemm_tile_dma<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR>(p, z, s, tm * BM, tn * BN);
-    else
-      gemm_tile_staged<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, ALIGNED>(p, z, s, tm * BM,
-                                                                               tn * BN);
-  };
-  one(slot);
+  one(slot, tn);
   if (fold && ntm - 1 - slot != slot) {
     __syncthreads();   // the second tile reuses the LDS stages
-    one(ntm - 1 - slot);
+    one(ntm - 1 - slot, tn);
   }
 }
 
@@ -938,10 +974,10 @@ __global__ __launch_bounds__(256) void gemm_direct_kernel(GemmParams<TIn, TCin, 
 }
 
 template <typename TIn, typename TCin, typename TCout, typename TC2,
-          int BM, int BN, int WGM, int WGN, bool BKMAJOR, bool ALIGNED, bool CLOWER = false>
+          int BM, int BN, int WGM, int WGN, bool BKMAJOR, int MODE, bool CLOWER = false>
 __global__ __launch_bounds__(WGM * WGN * 64, 2)
 void gemm_kernel(GemmParams<TIn, TCin, TCout, TC2> p) {
-  gemm_tile<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, ALIGNED, CLOWER>(
+  gemm_tile<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, MODE, CLOWER>(
       p, blockIdx.z, blockIdx.y, blockIdx.x, gridDim.x);
 }
 
@@ -980,7 +1016,7 @@ __global__ __launch_bounds__(256) void gemm_splitk_finish(GemmParams<TIn, TCin, 
 // grid.  Entry e owns workgroups [tile_start[e], tile_start[e+1]); within an
 // entry the workgroups cover ksplit x tiles (K slice, then tile).
 template <typename TIn, typename TCin, typename TCout, typename TC2,
-          int BM, int BN, int WGM, int WGN, bool BKMAJOR, bool ALIGNED>
+          int BM, int BN, int WGM, int WGN, bool BKMAJOR, int MODE>
 __global__ __launch_bounds__(WGM * WGN * 64, 2)
 void gemm_grouped_kernel(const GemmParams<TIn, TCin, TCout, TC2>* __restrict__ entries,
                          const int* __restrict__ tile_start, int nentries) {
@@ -994,21 +1030,33 @@ void gemm_grouped_kernel(const GemmParams<TIn, TCin, TCout, TC2>* __restrict__ e
   const GemmParams<TIn, TCin, TCout, TC2>& p = entries[lo];
   const int tiles = gemm_wgs(p.M, p.N, p.K, p.flags, BM, BN);
   const int local = b - tile_start[lo];
-  gemm_tile<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, ALIGNED>(p, 0, local / tiles,
-                                                                      local % tiles, tiles);
+  gemm_tile<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, MODE>(p, 0, local / tiles,
+                                                                   local % tiles, tiles);
 }
 
-// Whether the 16-byte vector path may be used for a product.
+// How a product's operands reach LDS.  Binary64/binary32: kDma16 if the rows of both
+// are 16-byte aligned, kDma16A if those of A are (batches: A is a packed inverted
+// block, B has the caller's leading dimension), else kDma4; kStaged only where a
+// tile's rows span more than a buffer descriptor.  Other types: kDma16 for the
+// 16-byte staged path, else kStaged.
 template <typename TIn, int BM, int BN, bool BKMAJOR, typename P>
-inline bool gemm_aligned(const P& p) {
+inline int gemm_mode(const P& p) {
   constexpr int VEC = 16 / sizeof(TIn);
   constexpr int BK = 128 / sizeof(TIn);
   auto al = [](const void* ptr) { return (reinterpret_cast<uintptr_t>(ptr) & 15) == 0; };
   const int64_t span_a = (int64_t)BM * p.lda * (int64_t)sizeof(TIn);
   const int64_t span_b = (int64_t)(BKMAJOR ? BN : BK) * p.ldb * (int64_t)sizeof(TIn);
-  return al(p.A) && al(p.B) && p.lda % VEC == 0 && p.ldb % VEC == 0 && p.sa_o % VEC == 0 &&
-         p.sa_i % VEC == 0 && p.sb_o % VEC == 0 && p.sb_i % VEC == 0 && p.K % VEC == 0 &&
-         (BKMAJOR || p.N % VEC == 0) && span_a < kBufOOB && span_b < kBufOOB;
+  if (span_a >= kBufOOB || span_b >= kBufOOB) return kStaged;
+  const bool a = al(p.A) && p.lda % VEC == 0 && p.sa_o % VEC == 0 && p.sa_i % VEC == 0;
+  const bool b = al(p.B) && p.ldb % VEC == 0 && p.sb_o % VEC == 0 && p.sb_i % VEC == 0;
+  if (a && b && p.K % VEC == 0 && (BKMAJOR || p.N % VEC == 0)) return kDma16;
+  if constexpr (Mfma<TIn>::kPerLane == 1) {
+    // K need not be a multiple of the piece: the last piece of a row then holds an
+    // element of A (it stays inside that 16-byte granule) and its rest is masked
+    if (a && !BKMAJOR) return kDma16A;
+    return kDma4;
+  }
+  return kStaged;
 }
 
 // Split-K policy: products with at most half of `target` workgroups split K into
@@ -1111,8 +1159,7 @@ inline int chain_ksplit(const P& p, int64_t wgs, int batch) {
   return best;
 }
 
-// Host-side launch helper.  Picks the aligned (16-byte vector) path when every
-// operand start, leading dimension and batch stride allows it.
+// Host-side launch helper.
 template <typename TIn, typename TCin, typename TCout, typename TC2,
           int BM, int BN, int WGM, int WGN, bool BKMAJOR>
 inline hipError_t launch_gemm(const GemmParams<TIn, TCin, TCout, TC2>& p, int batch,
@@ -1123,30 +1170,37 @@ inline hipError_t launch_gemm(const GemmParams<TIn, TCin, TCout, TC2>& p, int ba
     if (direct_ok<TIn>(p, batch))
       return launch_direct<TIn, TCin, TCout, TC2, BKMAJOR>(p, batch, stream);
   }
-  const bool aligned = gemm_aligned<TIn, BM, BN, BKMAJOR>(p);
+  const int mode = gemm_mode<TIn, BM, BN, BKMAJOR>(p);
+  constexpr bool kDirect = Mfma<TIn>::kPerLane == 1;
+  // operands that are not 16-byte aligned take 64 x 64 tiles: a large tile's 4-byte
+  // copies of two chunks would exceed the counter of outstanding copies, and
+  // staged through registers it is slower at every size (gemm_tile_dma)
+  if constexpr (kDirect && BM * BN > 64 * 64) {
+    if (mode != kDma16 && mode != kStaged)
+      return launch_gemm<TIn, TCin, TCout, TC2, 64, 64, 2, 2, BKMAJOR>(p, batch, stream);
+  }
   const int64_t tiles = gemm_wgs(p.M, p.N, p.K, p.flags, BM, BN);
   GemmParams<TIn, TCin, TCout, TC2> q = p;
   // one round of workgroups: two per compute unit for the 128 x 128 tiles,
   // four for the smaller ones (their registers and LDS allow it)
   const int target = (BM * BN >= 128 * 128) ? kSplitTarget : 2 * kSplitTarget;
-  const bool chain = BM * BN < 128 * 128 && aligned && Mfma<TIn>::kPerLane == 1;
+  const bool chain = BM * BN < 128 * 128 && kDirect && mode != kStaged;
   q.ksplit = chain ? chain_ksplit<TIn>(p, tiles * batch, batch)
                    : gemm_ksplit<TIn>(p, tiles * batch, batch, target);
   // lower-triangle products take their own instantiation (tile enumeration)
   const bool clower = p.flags & G_C_LOWER;
   dim3 grid((unsigned)tiles, (unsigned)q.ksplit, (unsigned)batch);
   dim3 block(WGM * WGN * 64);
-  if (clower) {
-    if (aligned)
-      gemm_kernel<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, true, true>
-          <<<grid, block, 0, stream>>>(q);
-    else
-      gemm_kernel<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, false, true>
-          <<<grid, block, 0, stream>>>(q);
-  } else if (aligned) {
-    gemm_kernel<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, true><<<grid, block, 0, stream>>>(q);
-  } else {
-    gemm_kernel<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, false><<<grid, block, 0, stream>>>(q);
+  auto go = [&](auto kernel) { kernel<<<grid, block, 0, stream>>>(q); };
+  if (mode == kDma16) {
+    if (clower) go(gemm_kernel<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, kDma16, true>);
+    else go(gemm_kernel<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, kDma16>);
+  } else if (mode == kStaged) {
+    if (clower) go(gemm_kernel<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, kStaged, true>);
+    else go(gemm_kernel<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, kStaged>);
+  } else if constexpr (kDirect && BM == 64 && BN == 64) {
+    if (clower) go(gemm_kernel<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, kDma4, true>);
+    else go(gemm_kernel<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, kDma4>);
   }
   if (q.ksplit > 1) {
     const int64_t total = (int64_t)p.M * p.N * batch;

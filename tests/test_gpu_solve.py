@@ -525,6 +525,42 @@ def test_batch_matches_oracle_and_is_mix_independent(torch, T, prec, n0, shapes)
 
 
 @pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("n0,shapes", [
+    (32, [(63, 33, 0, 0), (65, 63, 1, 0), (129, 65, 0, 1), (200, 130, 3, 3), (131, 5, 1, 1)]),
+    (128, [(1000, 64, 0, 0), (1002, 129, 2, 3), (999, 31, 1, 1), (515, 200, 0, 4)])])
+def test_grouped_products_at_tile_edges(torch, T, prec, n0, shapes):
+    # a batch's products take 128 x 32, 64 x 64 or 128 x 128 tiles, with operands
+    # copied 16 or 4 bytes a lane by their alignment: rows, columns and K one past
+    # or short of a tile and of a 16-byte piece, padded rows; nothing outside the
+    # matrices is used (NaN) or written
+    dt = torch.float64 if prec == "f64" else torch.float32
+    held, items = [], (T.BatchItem * len(shapes))()
+    for i, (n, k, padl, padk) in enumerate(shapes):
+        L, B = gen.easy_system(n, k, 5 * n + k, upper=np.nan)
+        if prec == "f32":
+            L, B = L.astype(np.float32).astype(np.float64), B.astype(np.float32).astype(np.float64)
+        Lf = torch.full((n, n + padl), float("nan"), dtype=dt, device="cuda")
+        Lf[:, :n] = dev(torch, L, dt)
+        Bf = torch.full((n, k + padk), float("nan"), dtype=dt, device="cuda")
+        Bf[:, :k] = dev(torch, B, dt)
+        Xf = torch.full((n, k + padk), -7.0, dtype=dt, device="cuda")
+        sv = T.Solver.create(n, k, prec, n0)
+        sv.invert(Lf[:, :n])
+        held.append((L, B, Lf, Bf, Xf, sv))
+        items[i] = T.BatchItem(n, k, Lf.data_ptr(), n + padl, sv.linv_ptr, Bf.data_ptr(), k + padk,
+                               Xf.data_ptr(), k + padk)
+    torch.cuda.synchronize()
+    b, ws, wsp = _run_batch(torch, T, items, prec, n0)
+    T.trsm_batch_check(b, wsp)
+    T.trsm_batch_destroy(b)
+    for (n, k, _, _), (L, B, _, _, Xf, sv) in zip(shapes, held):
+        err = oracle.rel_fro_err(host(Xf[:, :k]), oracle.trsm(L, B))
+        assert err <= (TOL64 if prec == "f64" else TOL32), (n, k)
+        assert bool((Xf[:, k:] == -7.0).all()), (n, k)
+        sv.close()
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
 def test_batch_autotune_choice_solves_the_batch(torch, T, prec):
     """trsm_batch_autotune times every candidate block size on synthetic
     systems of the batch's shapes, records the winner for trsm_batch_
