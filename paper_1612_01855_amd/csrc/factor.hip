@@ -338,10 +338,9 @@ struct Ctx {
 };
 
 // C = alpha * A op(B) (+ C when accumulate); op(B) = B^T stored as N x K rows
-// when BT.  Products with fewer than two 128 x 128 workgroups per compute
-// unit take 64 x 64 tiles (and split K when still small, if `split`: the
-// products inside a diagonal block are too small for the finishing pass to
-// pay off).
+// when BT.  Small products take 64 x 64 tiles (small_tile) and split K when
+// those are few, if `split`: the products inside a diagonal block are too small
+// for the finishing pass to pay off.
 template <bool BT>
 hipError_t prod(const Ctx& c, const double* A, int64_t lda, const double* B, int64_t ldb,
                 double* C, int64_t ldc, int64_t M, int64_t N, int64_t K, double alpha,
@@ -361,9 +360,8 @@ hipError_t prod(const Ctx& c, const double* A, int64_t lda, const double* B, int
   p.flags = flags;
   p.part = split ? c.split : nullptr;
   p.part_bytes = split ? (int64_t)c.split_bytes : 0;
-  const bool small = gemm_wgs(p.M, p.N, p.K, flags, 128, 128) < kSplitTarget;
-  return small ? launch_gemm<double, double, double, float, 64, 64, 2, 2, BT>(p, 1, c.s)
-               : launch_gemm<double, double, double, float, 128, 128, 2, 2, BT>(p, 1, c.s);
+  return small_tile<double>(p, 1) ? launch_gemm<double, double, double, float, 64, 64, 2, 2, BT>(p, 1, c.s)
+                                  : launch_gemm<double, double, double, float, 128, 128, 2, 2, BT>(p, 1, c.s);
 }
 
 #define CHOL_HIP(...)                                           \

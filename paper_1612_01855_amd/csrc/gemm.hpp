@@ -1159,6 +1159,19 @@ inline int chain_ksplit(const P& p, int64_t wgs, int batch) {
   return best;
 }
 
+// Tile of a binary64/binary32 product: 64 x 64 (else 128 x 128) below two 128 x 128
+// workgroups per compute unit, and for short K: a 128 x 128 workgroup's first
+// copies and its stores of C run beside one other workgroup, those of the 64 x 64
+// tiles beside three or four.  From K = 1024 (binary64) or 2048 (binary32) the
+// large tiles' fewer LDS reads count for more.  8192 x 8192 x K, 64 / 128 tiles, us:
+// binary64 K = 128 434 / 592, 512 1183 / 1204, 1024 2195 / 2112; binary32 128
+// 278 / 435, 512 633 / 773, 1024 1113 / 1194, 2048 2125 / 2149, 4096 4144 / 4119.
+template <typename TIn, typename P>
+inline bool small_tile(const P& p, int batch) {
+  return gemm_wgs(p.M, p.N, p.K, p.flags, 128, 128) * (int64_t)batch < kSplitTarget ||
+         p.K <= (sizeof(TIn) == 8 ? 512 : 1024);
+}
+
 // Host-side launch helper.
 template <typename TIn, typename TCin, typename TCout, typename TC2,
           int BM, int BN, int WGM, int WGN, bool BKMAJOR>

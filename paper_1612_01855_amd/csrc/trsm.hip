@@ -281,15 +281,11 @@ namespace {
 template <typename T>
 struct Gemm {
   using P = GemmParams<T, T, T, float>;
-  // Products that give fewer workgroups than two per compute unit with
-  // 128 x 128 tiles use 64 x 64 tiles (four times as many workgroups; the
-  // binary64/binary32 matrix-core rate per workgroup does not depend on the
-  // tile), and split K if they are still small.
+  // Small products use 64 x 64 tiles (small_tile), and split K if those are few.
   static hipError_t run(const P& p0, int batch, hipStream_t s) {
     P p = p0;
     use_split(p);
-    const bool small = !g_large_tiles &&
-                       (int64_t)gemm_wgs(p.M, p.N, p.K, p.flags, 128, 128) * batch < kSplitTarget;
+    const bool small = !g_large_tiles && small_tile<T>(p, batch);
     return timed(gemm_flops(p, batch), s, [&] {
       return small ? launch_gemm<T, T, T, float, 64, 64, 2, 2, false>(p, batch, s)
                    : launch_gemm<T, T, T, float, 128, 128, 2, 2, false>(p, batch, s);
@@ -574,10 +570,7 @@ trsm_status low_sweep_left(const trsm_plan_s& P, const float* Linv32, const TL* 
       p.Cout = D + r0 * k; p.ldco = k;
       p.M = (int)sz; p.N = (int)k; p.K = (int)sz;
       p.flags = G_A_LOWER | G_A_ZERO_UPPER;
-      use_split(p);
-      TRSM_HIP(timed(gemm_flops(p, 1), s, [&] {
-        return launch_gemm<float, float, float, float, 128, 128, 2, 2, false>(p, 1, s);
-      }));
+      TRSM_HIP(Gemm<float>::run(p, 1, s));
     }
     if (i + 1 < m)
       TRSM_HIP(launch_lowx<TL>(D + r0 * k, k, sz, k, XlowT + r0, n, amax + i, xinv + i, etarget, s));
@@ -611,10 +604,7 @@ trsm_status low_sweep(const trsm_plan_s& P, const float* Linv32, const TL* Llow,
       p.Cout = D + r0 * k; p.ldco = k;
       p.M = (int)sz; p.N = (int)k; p.K = (int)sz;
       p.flags = G_A_LOWER | G_A_ZERO_UPPER;
-      use_split(p);
-      TRSM_HIP(timed(gemm_flops(p, 1), s, [&] {
-        return launch_gemm<float, float, float, float, 128, 128, 2, 2, false>(p, 1, s);
-      }));
+      TRSM_HIP(Gemm<float>::run(p, 1, s));
     }
     if (i + 1 < m) {
       // XlowT(:, S_i) = low(2^e D(S_i))^T, then Rl(T_i+1) -= Llow * X(S_i)
