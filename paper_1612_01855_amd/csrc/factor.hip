@@ -21,7 +21,7 @@
 //   factor D22 -> L22, Linv22;   Linv21 = -(Linv22 L21) Linv11,
 //
 // the last line being Alg. RecTriInv's combine, so the inverse of the block
-// is built along the way; 64 x 64 leaves are factored and inverted in LDS.
+// is built along the way; leaves of 64 or 128 rows are factored and inverted in LDS.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -31,6 +31,7 @@
 
 #include "../../include/trsm.h"
 #include "common.hpp"
+#include "diag.hpp"
 #include "gemm.hpp"
 #include "kernels.hpp"
 
@@ -53,153 +54,120 @@ inline int64_t pow2_at_least(int64_t v) {
   return p;
 }
 
-// Value of lane `lane` (a wave-uniform constant) for every lane.
-__device__ __forceinline__ double lane_value(double v, int lane) {
-  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, lane);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), lane);
-  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-}
-
-// Leaf: the s x s (s <= 64) diagonal block D (lower triangle read) is
-// factored by wave 0 and inverted by wave 1, one step behind it.  Wave 0,
-// lane i holding row i of the block in registers (positions past s hold the
-// identity), right-looking, step j: every lane takes the pivot a_jj from
-// lane j, then
-//   l_jj = sqrt(a_jj),  l_ij = a_ij / l_jj   (column j published in LDS),
-//   a_ic -= l_ij l_cj                        for c > j.
-// Entries above the diagonal are updated too (they are never read), so no
-// lane is masked.  Wave 1, lane t holding column t of the inverse (starting
-// from the identity), takes column j of L from LDS in the next step:
-//   x_jt *= 1 / l_jj,   x_rt -= l_rj x_jt   for r > j,
-// i.e. x_rt = (delta_rt - sum_{p<r} l_rp x_pt) / l_rr with the sum taken in
-// p order.  The two waves share one register array (each uses it for its
-// own role).  L goes back to D's lower triangle (the strict upper triangle
-// is not written), the inverse to V (ld ldv; nothing above the diagonal is
-// written).  A pivot that is not positive (or NaN) records its global row in
-// *bad (the smallest one wins) and is replaced by 1 so that the arithmetic
-// stays finite.  LDS reads come in 16-byte pairs issued ahead of their use.
-constexpr int kLdc = kLeaf + 2;   // column stride of Lc (16-byte aligned rows)
-constexpr int kAhead = 8;         // LDS pair reads in flight
-constexpr int kGroup = 8;         // leaf steps between the two waves' barriers
-
-__global__ __launch_bounds__(2 * kLeaf) void chol_leaf_kernel(double* __restrict__ D,
-                                                              int64_t ldd, int s,
-                                                              double* __restrict__ V,
-                                                              int64_t ldv, int64_t row0,
-                                                              unsigned long long* bad) {
-  __shared__ __attribute__((aligned(16))) double Lc[kLeaf][kLdc];
-  __shared__ double rdiag[kLeaf];
-  typedef double D2 __attribute__((ext_vector_type(2)));
-  const int tid = threadIdx.x, i = tid % kLeaf;
-  const bool w0 = tid < kLeaf;    // wave 0 factors, wave 1 inverts
-  // coalesced load, all loads of a thread issued before any is used: thread
-  // (wave w, lane i) takes column i of rows w, w + 2, ...
-  {
-    double v[kLeaf / 2];
-#pragma unroll
-    for (int q = 0; q < kLeaf / 2; ++q) {
-      const int r = 2 * q + (w0 ? 0 : 1);
-      v[q] = (r < s && i <= r) ? D[(int64_t)r * ldd + i] : 0.0;
-    }
-#pragma unroll
-    for (int q = 0; q < kLeaf / 2; ++q) {
-      const int r = 2 * q + (w0 ? 0 : 1);
-      Lc[r][i] = (r >= s && r == i) ? 1.0 : v[q];
-    }
+// The elements of a 16 NT-row block that a thread of T carries between global
+// memory and LDS: column c of rows r0, r0 + kStep, ...
+template <int NT, int T>
+struct Carry {
+  static constexpr int kRows = 16 * NT, kStep = T / kRows, kEach = kRows / kStep;
+  int c, r0;
+  __device__ __forceinline__ Carry() {
+    int t = threadIdx.x;
+    // each use computes its addresses anew: kept from one to the next they would
+    // take the registers that the columns need
+    asm volatile("" : "+v"(t));
+    c = t % kRows;
+    r0 = t / kRows;
   }
-  __syncthreads();
-  double a[kLeaf];   // wave 0: row i of the block; wave 1: column i of the inverse
-  if (w0) {
+  // f(row, column, q, offset of the element in a matrix of leading dimension ld)
+  template <typename F>
+  __device__ __forceinline__ void each(int64_t ld, F f) const {
+    const int64_t o = r0 * ld + c, step = kStep * ld;
 #pragma unroll
-    for (int c = 0; c < kLeaf; c += 2) {
-      const D2 v = *reinterpret_cast<const D2*>(&Lc[i][c]);
-      a[c] = v.x;
-      a[c + 1] = v.y;
-    }
-  } else {
-#pragma unroll
-    for (int r = 0; r < kLeaf; ++r) a[r] = (r == i) ? 1.0 : 0.0;
+    for (int q = 0; q < kEach; ++q) f(r0 + q * kStep, c, q, o + q * step);
   }
-  __syncthreads();
-  // the loop is kept free of per-lane branches (they split it into blocks that
-  // the register allocator handles badly): failures are collected in `first`.
-  // Column j + 1 is finished and published right after its own update in
-  // step j, so its square root and division can overlap the rest of step j.
-  int first = kLeaf;
-  auto publish = [&](int j) {
-    double piv = lane_value(a[j], j);
-    const bool ok = piv > 0.0;
-    first = (!ok && first == kLeaf) ? j : first;
-    piv = ok ? piv : 1.0;
-    const double d = sqrt(piv);
-    const double l = (i == j) ? d : a[j] / d;
-    a[j] = l;
-    Lc[j][i] = l;
-    rdiag[j] = 1.0 / d;
-  };
-  if (w0) publish(0);
-  // Steps go in groups of kGroup between barriers: wave 0 factors group g
-  // while wave 1 inverts with the columns of group g - 1.
-#pragma unroll
-  for (int g = 0; g <= kLeaf / kGroup; ++g) {
-    if (w0 && g < kLeaf / kGroup) {
-#pragma unroll
-      for (int j = g * kGroup; j < (g + 1) * kGroup && j + 1 < kLeaf; ++j) {
-        const double l = a[j];
-        // l_{j+1,j} straight from lane j + 1: the next pivot's chain
-        // does not wait for LDS
-        a[j + 1] = fma(-l, lane_value(l, j + 1), a[j + 1]);
-        publish(j + 1);
-        // the rest of the row, c >= j + 2, in pairs read kAhead pairs ahead
-        const int q0 = (j + 2) / 2;
-        D2 buf[kLeaf / 2];
-#pragma unroll
-        for (int q = q0; q < kLeaf / 2 && q < q0 + kAhead; ++q)
-          buf[q] = *reinterpret_cast<const D2*>(&Lc[j][2 * q]);
-#pragma unroll
-        for (int q = q0; q < kLeaf / 2; ++q) {
-          if (q + kAhead < kLeaf / 2)
-            buf[q + kAhead] = *reinterpret_cast<const D2*>(&Lc[j][2 * (q + kAhead)]);
-          if (2 * q >= j + 2) a[2 * q] = fma(-l, buf[q].x, a[2 * q]);
-          a[2 * q + 1] = fma(-l, buf[q].y, a[2 * q + 1]);
-        }
+};
+
+// Leaf: the s x s diagonal block D (s <= 16 NT, lower triangle read) is factored
+// and inverted in LDS, 16 columns a step: the columns by waves with a row a lane
+// (chol_columns; with more than 48 rows below them the diagonal tile's rows are
+// worked on by every wave that needs them), the rest of the block by the matrix
+// cores, while wave 3 stores and inverts the last step's diagonal tile in place.
+// Then the inverse is completed as in Alg. RecTriInv (combine).  Positions past s hold
+// the identity.  L goes to D's lower triangle (the strict upper triangle is not
+// written), the inverse to V (ld ldv, nothing above the diagonal).  A pivot that is
+// not positive (or NaN) records its global row in *bad (the smallest one wins) and is
+// replaced by 1 so that the arithmetic goes on.
+//
+// Bound by the chain of columns.  128 rows take 55 us, where two leaves of 64 (one
+// wave for 64 columns one after the other, one for the inverse a step behind: 28 us,
+// 49 beside the trailing products) and the four products between them took 95.
+template <int NT>
+constexpr int kCholThreads = NT <= 4 ? 256 : 1024;
+
+template <int NT>
+__global__ __launch_bounds__(kCholThreads<NT>, 4) void chol_leaf_kernel(
+    double* __restrict__ D, int64_t ldd, int s, double* __restrict__ V, int64_t ldv, int64_t row0,
+    unsigned long long* bad) {
+  using namespace diag;
+  using Map = LowerTiles;
+  constexpr int T = kCholThreads<NT>, kWaves = T / 64;
+  constexpr bool kShared = NT > 4;   // the diagonal tile's rows in several waves
+  using C = Carry<NT, T>;
+  __shared__ __attribute__((aligned(16))) double S[Map::count(NT) * kTile];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  __builtin_amdgcn_s_setprio(3);   // before the trailing products' waves beside it
+  const int nt = (s + 15) >> 4;
+  auto at = [&](int r, int c) { return Map::at(S, r >> 4, min(c >> 4, r >> 4)) + (r & 15) * kTld + (c & 15); };
+  double v[C::kEach];
+  C().each(ldd, [&](int r, int c, int q, int64_t o) { v[q] = D[r < s && c <= r ? o : 0]; });
+  int first = C::kRows;
+#pragma unroll 1
+  for (int p = -1; p <= nt; ++p) {
+    // p < 0: the run through the code; p = nt: only the last tile's inversion
+    const bool panel = p < nt && (p < 0 || wave == 0 || p + 1 + 3 * wave < nt);
+    const int i = lane < 16 ? p : p + 3 * wave + (lane >> 4);   // this lane's tile row
+    double* row = Map::at(S, min(max(i, 0), nt - 1), max(p, 0)) + (lane & 15) * kTld;
+    double a[16];
+    if (panel) row_load(a, row);
+    if (kShared) __syncthreads();
+    if (panel) {
+      int b = 16;
+      const bool odd = chol_columns<true>(a, p < 0 ? 1 << (wave & 3) : 15, &b);
+      if (odd && p >= 0) {
+        row_load(a, row);
+        chol_columns<false>(a, 15, &b);
+        if (b < 16) first = min(first, 16 * p + b);
       }
+    } else if (wave == 3 && p >= 1) {
+      double* x = Map::at(S, p - 1, p - 1);
+      const int o = 16 * (p - 1), gi = lane & 15, g = lane >> 4;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int r = 4 * q + g;
+        if (gi <= r && o + r < s) D[(o + r) * ldd + o + gi] = x[r * kTld + gi];
+      }
+      invert_tile(x, false, false);
     }
-    if (!w0 && g >= 1) {
-#pragma unroll
-      for (int jj = (g - 1) * kGroup; jj < g * kGroup; ++jj) {
-        // column jj of L was published before the last barrier
-        a[jj] *= rdiag[jj];
-        const int q0 = (jj + 1) / 2;
-        D2 buf[kLeaf / 2];
-#pragma unroll
-        for (int q = q0; q < kLeaf / 2 && q < q0 + kAhead; ++q)
-          buf[q] = *reinterpret_cast<const D2*>(&Lc[jj][2 * q]);
-#pragma unroll
-        for (int q = q0; q < kLeaf / 2; ++q) {
-          if (q + kAhead < kLeaf / 2)
-            buf[q + kAhead] = *reinterpret_cast<const D2*>(&Lc[jj][2 * (q + kAhead)]);
-          if (2 * q > jj) a[2 * q] = fma(-buf[q].x, a[jj], a[2 * q]);
-          a[2 * q + 1] = fma(-buf[q].y, a[jj], a[2 * q + 1]);
-        }
-      }
+    if (kShared) __syncthreads();
+    if (p < 0) {
+      C().each(0, [&](int r, int c, int q, int64_t) {
+        if (c >> 4 <= r >> 4) *at(r, c) = r < s && c <= r ? v[q] : r == c ? 1.0 : 0.0;
+      });
+    } else if (panel && (lane < 16 ? wave == 0 : i < nt)) {
+      row_store(a, row);
+    }
+    __syncthreads();
+    if (p < 0) continue;
+    int e = wave;
+    for (int ti = p + 1; ti < nt; ++ti) {
+      for (; e <= ti - p - 1; e += kWaves)
+        tile_update<true>(Map::at(S, ti, p + 1 + e), Map::at(S, ti, p), Map::at(S, p + 1 + e, p));
+      e -= ti - p;
     }
     __syncthreads();
   }
   if (tid == 0 && first < s) atomicMin(bad, (unsigned long long)(row0 + first));
-  // L back to D, rows coalesced (element (r, i) is Lc[i][r]), both waves
-  for (int r = (w0 ? 0 : 1); r < s; r += 2)
-    if (i <= r) D[(int64_t)r * ldd + i] = Lc[i][r];
+  C().each(ldd, [&](int r, int c, int, int64_t o) {
+    const double x = *at(r, c);
+    if (r < s && c >> 4 < r >> 4) D[o] = x;
+  });
   __syncthreads();
-  // column i of the inverse through LDS, then coalesced rows (r >= i)
-  if (!w0) {
-#pragma unroll
-    for (int r = 0; r < kLeaf; ++r) Lc[r][i] = a[r];
-  }
-  __syncthreads();
-  for (int r = (w0 ? 0 : 1); r < kLeaf; r += 2)
-    if (i <= r) V[(int64_t)r * ldv + i] = Lc[r][i];
+  combine<Map, NT>(S, nt, false, false);
+  C().each(ldv, [&](int r, int c, int, int64_t o) {
+    const double x = *at(r, c);
+    if (r < s && c <= r) V[o] = x;
+  });
 }
 
 // Linv blocks: zero everywhere except the identity on the padded diagonal of
@@ -215,112 +183,110 @@ __global__ void chol_init_kernel(double* __restrict__ V, int64_t n, int64_t nb, 
   }
 }
 
-// LU leaf: the s x s (s <= 64) diagonal block D is factored without row
-// exchanges by four waves, right-looking, step j (u_jj the pivot):
-//   l_ij = d_ij / u_jj (i > j),  u_jc = d_jc (c >= j),  d_ic -= l_ij u_jc (i, c > j).
-// Wave 0 holds row i in lane i and publishes column j of L in LDS; wave 1
-// holds column c in lane c and publishes row j of U; after one barrier each
-// takes the other's half for its update (both compute the same products, so
-// their U parts stay bitwise equal; wave 1 never scales its entries below the
-// diagonal, which nothing reads), while wave 2 (column t of L^{-1}, unit
-// diagonal) and wave 3 (column t of (U^T)^{-1}, i.e. row t of U^{-1}) take
-// step j of their substitutions from the same two published vectors:
-//   x_rt -= l_rj x_jt (r > j);   z_jt /= u_jj,  z_rt -= u_jr z_jt (r > j).
-// Every wave consumes step j's vectors within step j, so two LDS slots per
-// vector suffice (2 KB in all: the leaf fits beside the trailing products'
-// workgroups); the block goes between global memory and registers directly.
-// Positions past s hold the identity.  L (strictly lower) and U go back to
-// D, the inverses to VL (unit lower, diagonal stored) and VU (upper), ld ldv,
-// nothing written on their other side.  A zero or non-finite pivot records
-// its global row in *bad (the smallest one wins) and is replaced by 1 in the
-// divisions of L.  LDS reads come in 16-byte pairs issued ahead of their use.
-__global__ __launch_bounds__(4 * kLeaf) void lu_leaf_kernel(double* __restrict__ D,
-                                                            int64_t ldd, int s,
-                                                            double* __restrict__ VL,
-                                                            double* __restrict__ VU,
-                                                            int64_t ldv, int64_t row0,
-                                                            unsigned long long* bad) {
-  __shared__ __attribute__((aligned(16))) double Lr[2][kLdc];   // slot: l_rj, column j of L
-  __shared__ __attribute__((aligned(16))) double Ur[2][kLdc];   // slot: u_jc, row j of U
-  typedef double D2 __attribute__((ext_vector_type(2)));
-  const int tid = threadIdx.x, w = tid / kLeaf, i = tid % kLeaf;
-  // wave 0: row i; wave 1: column i; waves 2, 3: column i of the identity
-  double a[kLeaf];
-  if (w == 0) {
+// LU leaf: the s x s (s <= 64) diagonal block D is factored without row exchanges
+// and both factors are inverted in LDS, as in chol_leaf_kernel: 16 columns of L and
+// the 16 rows of U beside them by wave 0 (lu_columns), the rest of the block by the
+// matrix cores, the last step's diagonal tile inverted in place by waves 2 (L) and 3
+// (U), and the inverses completed by combine.  Positions past s hold the identity.
+// L (strictly lower) and U go back to D, the inverses to VL (unit lower, diagonal
+// stored) and VU (upper), ld ldv, nothing written on their other side.  A zero or
+// non-finite pivot records its global row in *bad (the smallest one wins) and is
+// replaced by 1 in the divisions of L.
+//
+// Four waves, 37 KB: the size of one workgroup of the trailing products, whose place
+// it takes when it runs beside them.  Bound by the chain of columns: 37 us (four
+// waves exchanging 64 columns one after the other through LDS: 57).  Beside the
+// trailing products it takes up to 130 us, as their matrix instructions use the same
+// binary64 units; more LDS, to keep their workgroups off the compute unit, made it
+// wait longer for its place than it gained (8192 rows: 15.4 ms; 96 or 129 KB 16.5).
+constexpr int kLuTiles = kLeaf / 16;
+
+__global__ __launch_bounds__(256, 4) void lu_leaf_kernel(double* __restrict__ D, int64_t ldd, int s,
+                                                      double* __restrict__ VL,
+                                                      double* __restrict__ VU, int64_t ldv,
+                                                      int64_t row0, unsigned long long* bad) {
+  using namespace diag;
+  using Map = AllTiles<kLuTiles>;
+  using C = Carry<kLuTiles, 256>;
+  __shared__ __attribute__((aligned(16))) double S[Map::count(kLuTiles) * kTile];
+  const int tid = threadIdx.x, lane = tid & 63, gi = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  __builtin_amdgcn_s_setprio(3);   // before the trailing products' waves beside it
+  const int nt = (s + 15) >> 4;
+  auto at = [&](int r, int c) { return Map::at(S, r >> 4, c >> 4) + (r & 15) * kTld + (c & 15); };
+  double v[C::kEach];
+  C().each(ldd, [&](int r, int c, int q, int64_t o) { v[q] = D[r < s && c < s ? o : 0]; });
+  int first = C::kRows;
+#pragma unroll 1
+  for (int p = -1; p <= nt; ++p) {
+    // p < 0: the run through the code; p = nt: only the last tile's inversions
+    if (p < nt && (p < 0 || wave == 0)) {
+      // lanes 0 to 15 the diagonal tile's rows, lane group t the rows of the t-th tile
+      // below and the columns of the t-th tile to the right
+      const int pp = max(p, 0), other = min(pp + g, nt - 1);
+      double* row = Map::at(S, other, pp) + gi * kTld;
+      double* col = Map::at(S, pp, other) + gi;
+      double a[16], b[16];
+      auto load = [&] {
+        row_load(a, row);
 #pragma unroll
-    for (int c = 0; c < kLeaf; ++c)
-      a[c] = (i < s && c < s) ? D[(int64_t)i * ldd + c] : (c == i ? 1.0 : 0.0);
-  } else if (w == 1) {
+        for (int k = 0; k < 16; ++k) b[k] = col[k * kTld];
+      };
+      load();
+      int f = 16;
+      const bool odd = lu_columns<true>(a, b, p < 0 ? 1 << wave : 15, &f);
+      if (p >= 0) {
+        if (odd) {
+          load();
+          lu_columns<false>(a, b, 15, &f);
+          if (f < 16) first = min(first, 16 * p + f);
+        }
+        if (p + g < nt) row_store(a, row);
+        if (g > 0 && p + g < nt) {
 #pragma unroll
-    for (int r = 0; r < kLeaf; ++r)
-      a[r] = (r < s && i < s) ? D[(int64_t)r * ldd + i] : (r == i ? 1.0 : 0.0);
-  } else {
+          for (int k = 0; k < 16; ++k) col[k * kTld] = b[k];
+        }
+      }
+    } else if (wave >= 2 && p >= 1) {
+      double* x = Map::at(S, p - 1, p - 1);
+      const int o = 16 * (p - 1);
+      const bool upper = wave == 3;
 #pragma unroll
-    for (int r = 0; r < kLeaf; ++r) a[r] = (r == i) ? 1.0 : 0.0;
-  }
-  int first = kLeaf;
-  // a[c] -= m * P[c] for c > j, P a published LDS vector read in pairs
-  auto axpy = [&](const double* P, double m, int j) {
-    const int q0 = (j + 1) / 2;
-    D2 buf[kLeaf / 2];
-#pragma unroll
-    for (int q = q0; q < kLeaf / 2 && q < q0 + kAhead; ++q)
-      buf[q] = *reinterpret_cast<const D2*>(P + 2 * q);
-#pragma unroll
-    for (int q = q0; q < kLeaf / 2; ++q) {
-      if (q + kAhead < kLeaf / 2) buf[q + kAhead] = *reinterpret_cast<const D2*>(P + 2 * (q + kAhead));
-      if (2 * q > j) a[2 * q] = fma(-m, buf[q].x, a[2 * q]);
-      a[2 * q + 1] = fma(-m, buf[q].y, a[2 * q + 1]);
+      for (int q = 0; q < 4; ++q) {
+        const int r = 4 * q + g;
+        if ((upper ? gi >= r : gi < r) && o + r < s && o + gi < s)
+          D[(o + r) * ldd + o + gi] = x[r * kTld + gi];
+      }
+      invert_tile(x, upper, !upper);
     }
-  };
-#pragma unroll
-  for (int j = 0; j < kLeaf; ++j) {
-    const int slot = j & 1;
-    if (w == 0) {
-      double piv = lane_value(a[j], j);
-      const bool ok = (piv != 0.0) && isfinite(piv);
-      first = (!ok && first == kLeaf) ? j : first;
-      piv = ok ? piv : 1.0;
-      const double l = (i > j) ? a[j] / piv : 0.0;
-      a[j] = (i > j) ? l : a[j];
-      Lr[slot][i] = l;
-    } else if (w == 1) {
-      Ur[slot][i] = a[j];
+    if (p < 0) {
+      C().each(0, [&](int r, int c, int q, int64_t) {
+        *at(r, c) = r < s && c < s ? v[q] : r == c ? 1.0 : 0.0;
+      });
     }
     __syncthreads();
-    if (w == 0) {
-      axpy(&Ur[slot][0], (i > j) ? a[j] : 0.0, j);         // row i: -= l_ij u_j.
-    } else if (w == 1) {
-      const double u = (i > j) ? a[j] : 0.0;               // column i: -= l_.j u_ji
-#pragma unroll
-      for (int q = (j + 1) / 2; q < kLeaf / 2; ++q) {
-        const D2 v = *reinterpret_cast<const D2*>(&Lr[slot][2 * q]);
-        if (2 * q > j) a[2 * q] = fma(-v.x, u, a[2 * q]);
-        a[2 * q + 1] = fma(-v.y, u, a[2 * q + 1]);
-      }
-    } else if (w == 2) {
-      axpy(&Lr[slot][0], a[j], j);                         // x_r -= l_rj x_j
-    } else {
-      a[j] = a[j] / Ur[slot][j];                           // z_j /= u_jj
-      axpy(&Ur[slot][0], a[j], j);                         // z_r -= u_jr z_j
+    if (p < 0) continue;
+    int e = wave;
+    for (int ti = p + 1; ti < nt; ++ti) {
+      for (; e < nt - p - 1; e += 4)
+        tile_update<false>(Map::at(S, ti, p + 1 + e), Map::at(S, ti, p), Map::at(S, p, p + 1 + e));
+      e -= nt - p - 1;
     }
+    __syncthreads();
   }
   if (tid == 0 && first < s) atomicMin(bad, (unsigned long long)(row0 + first));
-  if (w == 0) {
-    if (i < s) {
-#pragma unroll
-      for (int c = 0; c < kLeaf; ++c)
-        if (c < s) D[(int64_t)i * ldd + c] = a[c];
-    }
-  } else if (w == 2) {
-#pragma unroll
-    for (int r = 0; r < kLeaf; ++r)
-      if (r >= i) VL[(int64_t)r * ldv + i] = a[r];
-  } else if (w == 3) {
-#pragma unroll
-    for (int c = 0; c < kLeaf; ++c)
-      if (c >= i) VU[(int64_t)i * ldv + c] = a[c];
-  }
+  C().each(ldd, [&](int r, int c, int, int64_t o) {
+    const double x = *at(r, c);
+    if (r < s && c < s && c >> 4 != r >> 4) D[o] = x;
+  });
+  __syncthreads();
+#pragma unroll 1
+  for (int u = 0; u < 2; ++u) combine<Map, kLuTiles>(S, nt, u, !u);
+  C().each(ldv, [&](int r, int c, int, int64_t o) {
+    const double x = *at(r, c);
+    if (r < s && c <= r) VL[o] = c == r ? 1.0 : x;
+    if (r <= c && c < s) VU[o] = x;
+  });
 }
 
 struct Ctx {
@@ -381,8 +347,14 @@ hipError_t prod(const Ctx& c, const double* A, int64_t lda, const double* B, int
 trsm_status factor_diag(const Ctx& c, int64_t r0, int64_t s, double* V) {
   const int64_t lda = c.lda, nb = c.nb;
   double* D = c.A + r0 * lda + r0;
-  if (s <= kLeaf) {
-    chol_leaf_kernel<<<1, 2 * kLeaf, 0, c.s>>>(D, lda, (int)s, V, nb, r0, c.bad);
+  // 128 rows at once only where they are a whole block: their 83 KB and 16 waves
+  // do not find a place beside the trailing products, and a block's first leaf
+  // starts before those
+  if (s <= kLeaf || (s <= 2 * kLeaf && nb <= 2 * kLeaf)) {
+    if (s <= kLeaf)
+      chol_leaf_kernel<4><<<1, kCholThreads<4>, 0, c.s>>>(D, lda, (int)s, V, nb, r0, c.bad);
+    else
+      chol_leaf_kernel<8><<<1, kCholThreads<8>, 0, c.s>>>(D, lda, (int)s, V, nb, r0, c.bad);
     CHOL_HIP(hipGetLastError());
     return TRSM_OK;
   }
@@ -546,7 +518,7 @@ trsm_status lu_factor_diag(const Ctx& c, int64_t r0, int64_t s, double* VL, doub
   const int64_t lda = c.lda, nb = c.nb;
   double* D = c.A + r0 * lda + r0;
   if (s <= kLeaf) {
-    lu_leaf_kernel<<<1, 4 * kLeaf, 0, c.s>>>(D, lda, (int)s, VL, VU, nb, r0, c.bad);
+    lu_leaf_kernel<<<1, 256, 0, c.s>>>(D, lda, (int)s, VL, VU, nb, r0, c.bad);
     CHOL_HIP(hipGetLastError());
     return TRSM_OK;
   }

@@ -144,9 +144,9 @@ __global__ __launch_bounds__(kInvThreads) void block_inverse_kernel(
   }
   __syncthreads();
   const int wave = tid >> 6;
-  if (wave < ntile) invert_tile<false, false>(Map::at(S, wave, wave));
+  if (wave < ntile) invert_tile(Map::at(S, wave, wave), false, false);
   __syncthreads();
-  combine<Map, kInvNt, false, false>(S, ntile);
+  combine<Map, kInvNt>(S, ntile, false, false);
   double* __restrict__ o = out + ((int64_t)s0 * n0 + fast);
 #pragma unroll
   for (int q = 0; q < kEach; ++q) {

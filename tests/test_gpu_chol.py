@@ -97,6 +97,28 @@ def test_leaf_sizes_are_exact_on_integer_factors(torch, T):
     assert np.array_equal(L, L0)
 
 
+@pytest.mark.parametrize("n", [2, 15, 16, 17, 48, 49, 64, 65, 80, 81, 112, 113, 127, 128])
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -920, 2.0 ** 920])
+def test_leaf_tiles(torch, T, n, scale):
+    # one block, factored and inverted in LDS in steps of 16 columns (up to 64 rows
+    # by 4 waves, up to 128 by 16, the rows below a step in one wave or several):
+    # edges of tiles and waves, and pivots outside the range of the fast roots
+    # (scale a power of four: every operation scales exactly, so the bound is the same)
+    A = gen.spd(n, 11 * n)
+    L, full, Vb, c = gpu_factor(torch, T, A * scale, 0 if n <= 64 else 128, lda=n + 3)
+    assert c.check() == (T.OK, -1)
+    Lref, _ = oracle.chol(A)
+    assert oracle.rel_fro_err(L / np.sqrt(scale), Lref) <= TOL64
+    assert np.all(np.isnan(full[np.triu_indices(n, 1)])) and np.all(np.isnan(full[:, n:]))
+    inv = oracle.diag_block_inverses(Lref, c.nb)[0]
+    assert oracle.rel_fro_err(Vb[0][:n, :n] * np.sqrt(scale), inv) <= TOL64
+    for bad in {0, n // 2, n - 1}:
+        A2 = A.copy()
+        A2[bad, bad] = -1.0
+        _, _, _, c = gpu_factor(torch, T, A2 * scale, 0 if n <= 64 else 128)
+        assert c.check() == (T.ESINGULAR, bad)
+
+
 @pytest.mark.parametrize("n,nb,bad", [(50, 0, 17), (300, 64, 0), (300, 64, 200),
                                       (1000, 256, 999), (1000, 256, 512)])
 def test_not_positive_definite_reports_the_row(torch, T, n, nb, bad):

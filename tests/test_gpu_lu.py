@@ -94,6 +94,29 @@ def test_leaf_sizes_are_exact_on_integer_factors(torch, T):
     assert np.array_equal(L, L0) and np.array_equal(U, U0)
 
 
+@pytest.mark.parametrize("n", [2, 15, 16, 17, 31, 33, 48, 49, 63, 64])
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -960, 2.0 ** 960])
+def test_leaf_tiles(torch, T, n, scale):
+    # one block, factored and inverted in LDS in steps of 16 columns: edges of
+    # tiles, and pivots outside the range of the fast quotients (the scale is a power of
+    # two: every operation scales exactly, so the bound is the same)
+    A = gen.diag_dominant(n, 11 * n)
+    L, U, full, f = gpu_lu(torch, T, A * scale, lda=n + 3)
+    assert f.check() == (T.OK, -1)
+    Lr, Ur, _ = oracle.lu_nopiv(A)
+    assert oracle.rel_fro_err(L, Lr) <= TOL64 and oracle.rel_fro_err(U / scale, Ur) <= TOL64
+    assert np.all(full[:, n:] == 7.0)
+    VL, VU = f.linv_blocks().cpu().numpy()[0], f.uinv_blocks().cpu().numpy()[0]
+    assert oracle.rel_fro_err(VL[:n, :n], oracle.inv_lower(Lr)) <= TOL64
+    iu = oracle.inv_lower(np.ascontiguousarray(Ur.T)).T
+    assert oracle.rel_fro_err(VU[:n, :n] * scale, iu) <= TOL64
+    for bad in {0, n // 2, n - 1}:
+        A2 = A.copy()
+        A2[bad, bad] = np.nan
+        _, _, _, f = gpu_lu(torch, T, A2 * scale)
+        assert f.check() == (T.ESINGULAR, bad)
+
+
 @pytest.mark.parametrize("n,nb,bad", [(50, 0, 17), (300, 64, 0), (300, 64, 200),
                                       (1000, 256, 999), (1000, 256, 512)])
 def test_bad_pivot_reports_the_row(torch, T, n, nb, bad):
