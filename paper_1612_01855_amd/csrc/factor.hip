@@ -307,10 +307,11 @@ struct Ctx {
 // when BT.  Small products take 64 x 64 tiles (small_tile) and split K when
 // those are few, if `split`: the products inside a diagonal block are too small
 // for the finishing pass to pay off.
-template <bool BT>
-hipError_t prod(const Ctx& c, const double* A, int64_t lda, const double* B, int64_t ldb,
-                double* C, int64_t ldc, int64_t M, int64_t N, int64_t K, double alpha,
-                bool accumulate, uint32_t flags, bool split = true) {
+GemmParams<double, double, double, float> prod_params(const Ctx& c, const double* A, int64_t lda,
+                                                      const double* B, int64_t ldb, double* C,
+                                                      int64_t ldc, int64_t M, int64_t N, int64_t K,
+                                                      double alpha, bool accumulate,
+                                                      uint32_t flags, bool split) {
   auto p = gemm_params<double, double, double, float>();
   p.A = A; p.lda = lda;
   p.B = B; p.ldb = ldb;
@@ -326,6 +327,14 @@ hipError_t prod(const Ctx& c, const double* A, int64_t lda, const double* B, int
   p.flags = flags;
   p.part = split ? c.split : nullptr;
   p.part_bytes = split ? (int64_t)c.split_bytes : 0;
+  return p;
+}
+
+template <bool BT>
+hipError_t prod(const Ctx& c, const double* A, int64_t lda, const double* B, int64_t ldb,
+                double* C, int64_t ldc, int64_t M, int64_t N, int64_t K, double alpha,
+                bool accumulate, uint32_t flags, bool split = true) {
+  const auto p = prod_params(c, A, lda, B, ldb, C, ldc, M, N, K, alpha, accumulate, flags, split);
   return small_tile<double>(p, 1) ? launch_gemm<double, double, double, float, 64, 64, 2, 2, BT>(p, 1, c.s)
                                   : launch_gemm<double, double, double, float, 128, 128, 2, 2, BT>(p, 1, c.s);
 }
@@ -481,7 +490,6 @@ trsm_status factor_lookahead(const Ctx& c, Side& sd) {
     double* A22 = A21 + s;
     if (pending) CHOL_HIP(hipStreamWaitEvent(c.s, sd.ev[2], 0));
     CHOL_HIP(prod<true>(c, A21, lda, Vj, nb, P, nb, t, s, s, 1.0, false, 0u));
-    CHOL_HIP(launch_copy2d<double, double>(P, nb, A21, lda, t, s, 1.0, c.s));
     const int64_t s1 = std::min(nb, t);
     // the next diagonal block, lower triangle, on the chain
     CHOL_HIP(prod<true>(c, P, nb, P, nb, A22, lda, s1, s1, s, -1.0, true, G_C_LOWER));
@@ -498,6 +506,8 @@ trsm_status factor_lookahead(const Ctx& c, Side& sd) {
     } else {
       pending = false;
     }
+    // the panel into A, off the chain: nothing reads it there before the end
+    CHOL_HIP(launch_copy2d<double, double>(P, nb, A21, lda, t, s, 1.0, t > s1 ? s2 : c.s));
   }
   // join: the caller's stream sees the side stream's work
   CHOL_HIP(hipEventRecord(sd.ev[2], s2));
@@ -528,33 +538,38 @@ trsm_status lu_factor_diag(const Ctx& c, int64_t r0, int64_t s, double* VL, doub
   double* D21 = D + h * lda;
   double* D22 = D21 + h;
   CHOL_TRY(lu_factor_diag(c, r0, h, VL, VU));
-  // L21 = D21 Uinv11 and U12 = Linv11 D12.  With h <= 64 each product has
-  // one tile along the dimension it overwrites (columns of L21, rows of U12),
-  // so every workgroup reads its part of the operand in full before writing
-  // it and the product runs in place; otherwise it goes through W.
+  // L21 = D21 Uinv11 and U12 = Linv11 D12, in one launch.  With h <= 64 each product
+  // has few enough columns (L21) or rows (U12) to run in place (launch_strips);
+  // otherwise they go through W (L21 in its first t rows, U12 below).
+  double* W1 = c.W + t * nb;
+  const double *L21 = D21, *U12 = D12;
+  int64_t ld21 = lda, ld12 = lda;
+  const uint32_t lower = G_A_LOWER | G_A_ZERO_UPPER;
   if (h <= kLeaf) {
-    CHOL_HIP(prod<false>(c, D21, lda, VU, nb, D21, lda, t, h, h, 1.0, false, 0u, false));
-    CHOL_HIP(prod<false>(c, VL, nb, D12, lda, D12, lda, h, t, h, 1.0, false,
-                         G_A_LOWER | G_A_ZERO_UPPER, false));
+    CHOL_HIP(launch_strips<double>(
+        prod_params(c, D21, lda, VU, nb, D21, lda, t, h, h, 1.0, false, 0u, false),
+        prod_params(c, VL, nb, D12, lda, D12, lda, h, t, h, 1.0, false, lower, false), c.s));
   } else {
-    CHOL_HIP(prod<false>(c, D21, lda, VU, nb, c.W, nb, t, h, h, 1.0, false, 0u, false));
+    CHOL_HIP(launch_pair<double>(
+        prod_params(c, D21, lda, VU, nb, c.W, nb, t, h, h, 1.0, false, 0u, false),
+        prod_params(c, VL, nb, D12, lda, W1, nb, h, t, h, 1.0, false, lower, false), c.s));
     CHOL_HIP(launch_copy2d<double, double>(c.W, nb, D21, lda, t, h, 1.0, c.s));
-    CHOL_HIP(prod<false>(c, VL, nb, D12, lda, c.W, nb, h, t, h, 1.0, false,
-                         G_A_LOWER | G_A_ZERO_UPPER, false));
-    CHOL_HIP(launch_copy2d<double, double>(c.W, nb, D12, lda, h, t, 1.0, c.s));
+    CHOL_HIP(launch_copy2d<double, double>(W1, nb, D12, lda, h, t, 1.0, c.s));
+    L21 = c.W;
+    U12 = W1;
+    ld21 = ld12 = nb;
   }
   // D22 -= L21 U12
-  CHOL_HIP(prod<false>(c, D21, lda, D12, lda, D22, lda, t, t, h, -1.0, true, 0u, false));
+  CHOL_HIP(prod<false>(c, L21, ld21, U12, ld12, D22, lda, t, t, h, -1.0, true, 0u, false));
   CHOL_TRY(lu_factor_diag(c, r0 + h, t, VL + h * nb + h, VU + h * nb + h));
-  // Linv21 = -(Linv22 L21) Linv11
-  CHOL_HIP(prod<false>(c, VL + h * nb + h, nb, D21, lda, c.W, nb, t, h, t, 1.0, false,
-                       G_A_LOWER | G_A_ZERO_UPPER, false));
-  CHOL_HIP(prod<false>(c, c.W, nb, VL, nb, VL + h * nb, nb, t, h, h, -1.0, false, G_B_LOWER,
-                       false));
-  // Uinv12 = -(Uinv11 U12) Uinv22
-  CHOL_HIP(prod<false>(c, VU, nb, D12, lda, c.W, nb, h, t, h, 1.0, false, G_A_UPPER, false));
-  CHOL_HIP(prod<false>(c, c.W, nb, VU + h * nb + h, nb, VU + h, nb, h, t, t, -1.0, false, 0u,
-                       false));
+  // Linv21 = -(Linv22 L21) Linv11 and Uinv12 = -(Uinv11 U12) Uinv22, side by side
+  CHOL_HIP(launch_pair<double>(
+      prod_params(c, VL + h * nb + h, nb, D21, lda, c.W, nb, t, h, t, 1.0, false, lower, false),
+      prod_params(c, VU, nb, D12, lda, W1, nb, h, t, h, 1.0, false, G_A_UPPER, false), c.s));
+  CHOL_HIP(launch_pair<double>(
+      prod_params(c, c.W, nb, VL, nb, VL + h * nb, nb, t, h, h, -1.0, false, G_B_LOWER, false),
+      prod_params(c, W1, nb, VU + h * nb + h, nb, VU + h, nb, h, t, t, -1.0, false, 0u, false),
+      c.s));
   return TRSM_OK;
 }
 
@@ -563,6 +578,19 @@ trsm_status lu_init(const Ctx& c, int64_t m) {
   Ctx cu = c;
   cu.V = c.VU;
   return init(cu, m);
+}
+
+// The panels L(T_j, S_j) = A(T_j, S_j) Uinv_jj into PL (ld nb) and U(S_j, T_j) =
+// Linv_jj A(S_j, T_j) into PU (ld n - nb): t rows and columns, in one launch.  7168 rows and columns, K = 256:
+// 38 us, one after the other 50.
+trsm_status lu_panels(const Ctx& c, const double* A21, const double* A12, const double* VL,
+                      const double* VU, double* PL, double* PU, int64_t s, int64_t t) {
+  const int64_t nb = c.nb, ldu = c.n - nb;
+  const auto pl = prod_params(c, A21, c.lda, VU, nb, PL, nb, t, s, s, 1.0, false, 0u, true);
+  const auto pu = prod_params(c, VL, nb, A12, c.lda, PU, ldu, s, t, s, 1.0, false,
+                              G_A_LOWER | G_A_ZERO_UPPER, true);
+  CHOL_HIP(launch_pair<double>(pl, pu, c.s));
+  return TRSM_OK;
 }
 
 // One stream: diagonal block, both panels, trailing update, in order.
@@ -580,10 +608,8 @@ trsm_status lu_factor_serial(const Ctx& c) {
     double* A22 = A21 + s;
     const int64_t ldu = n - nb;
     // L(T_j, S_j) = A(T_j, S_j) Uinv_jj;  U(S_j, T_j) = Linv_jj A(S_j, T_j)
-    CHOL_HIP(prod<false>(c, A21, lda, VUj, nb, c.W2[0], nb, t, s, s, 1.0, false, 0u));
+    CHOL_TRY(lu_panels(c, A21, A12, VLj, VUj, c.W2[0], c.WU[0], s, t));
     CHOL_HIP(launch_copy2d<double, double>(c.W2[0], nb, A21, lda, t, s, 1.0, c.s));
-    CHOL_HIP(prod<false>(c, VLj, nb, A12, lda, c.WU[0], ldu, s, t, s, 1.0, false,
-                         G_A_LOWER | G_A_ZERO_UPPER));
     CHOL_HIP(launch_copy2d<double, double>(c.WU[0], ldu, A12, lda, s, t, 1.0, c.s));
     // A(T_j, T_j) -= L(T_j, S_j) U(S_j, T_j)
     CHOL_HIP(prod<false>(c, c.W2[0], nb, c.WU[0], ldu, A22, lda, t, t, s, -1.0, true, 0u));
@@ -619,11 +645,7 @@ trsm_status lu_factor_lookahead(const Ctx& c, Side& sd) {
     double* A21 = c.A + (r0 + s) * lda + r0;
     double* A22 = A21 + s;
     if (pending) CHOL_HIP(hipStreamWaitEvent(c.s, sd.ev[2], 0));
-    CHOL_HIP(prod<false>(c, A21, lda, VUj, nb, PL, nb, t, s, s, 1.0, false, 0u));
-    CHOL_HIP(launch_copy2d<double, double>(PL, nb, A21, lda, t, s, 1.0, c.s));
-    CHOL_HIP(prod<false>(c, VLj, nb, A12, lda, PU, ldu, s, t, s, 1.0, false,
-                         G_A_LOWER | G_A_ZERO_UPPER));
-    CHOL_HIP(launch_copy2d<double, double>(PU, ldu, A12, lda, s, t, 1.0, c.s));
+    CHOL_TRY(lu_panels(c, A21, A12, VLj, VUj, PL, PU, s, t));
     const int64_t s1 = std::min(nb, t);
     // the next diagonal block on the chain
     CHOL_HIP(prod<false>(c, PL, nb, PU, ldu, A22, lda, s1, s1, s, -1.0, true, 0u));
@@ -640,6 +662,10 @@ trsm_status lu_factor_lookahead(const Ctx& c, Side& sd) {
     } else {
       pending = false;
     }
+    // the panels into A, off the chain: nothing reads them there before the end
+    const hipStream_t sc = t > s1 ? s2 : c.s;
+    CHOL_HIP(launch_copy2d<double, double>(PL, nb, A21, lda, t, s, 1.0, sc));
+    CHOL_HIP(launch_copy2d<double, double>(PU, ldu, A12, lda, s, t, 1.0, sc));
   }
   CHOL_HIP(hipEventRecord(sd.ev[2], s2));
   CHOL_HIP(hipStreamWaitEvent(c.s, sd.ev[2], 0));

@@ -853,10 +853,16 @@ __device__ __forceinline__ void gemm_tile(const GemmParams<TIn, TCin, TCout, TC2
 // ones multiply, and four times as many workgroups as 64 x 64 tiles.  VEC16:
 // operands with contiguous k are read 16 bytes at a time (aligned); otherwise
 // one element at a time, any alignment.  Triangles are skipped and masked per
-// 16 x 16 tile.  C must not overlap A or B.
+// 16 x 16 tile.  C must not overlap A or B, but for the strips: kRowStrip
+// (kColStrip), for products of at most 64 columns (rows), gives a workgroup 16 rows
+// (columns) of C in full, and its waves have read all they need of A (B) before the
+// first of them writes, so C may be A (B) itself.
+constexpr int kRowStrip = -1, kColStrip = -2;
+
 template <typename TIn, typename TCin, typename TCout, typename TC2, bool BKMAJOR, bool VEC16,
           int KW>
-__global__ __launch_bounds__(256) void gemm_direct_kernel(GemmParams<TIn, TCin, TCout, TC2> p) {
+__device__ __forceinline__ void gemm_direct_tile(const GemmParams<TIn, TCin, TCout, TC2>& p,
+                                                 int bid, int z) {
   using MF = Mfma<TIn>;
   using Out = typename MF::Out;
   using V16 = typename VecOf<TIn>::T2;
@@ -866,18 +872,22 @@ __global__ __launch_bounds__(256) void gemm_direct_kernel(GemmParams<TIn, TCin, 
   static_assert(MF::kPerLane == 1, "one k per lane and instruction");
   const int lane = threadIdx.x & 63, gi = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int z = blockIdx.z, zo = z / p.zdiv, zi = z % p.zdiv;
+  const int zo = z / p.zdiv, zi = z % p.zdiv;
   const int M = p.M, N = p.N, K = p.K;
   const int ntn = (N + 15) / 16, ntm = (M + 15) / 16;
   int tm, tn;
   if (KW == 1) {
     const int gn = (ntn + 1) / 2;
-    tm = 2 * ((int)blockIdx.x / gn) + (wave >> 1);
-    tn = 2 * ((int)blockIdx.x % gn) + (wave & 1);
+    tm = 2 * (bid / gn) + (wave >> 1);
+    tn = 2 * (bid % gn) + (wave & 1);
+  } else if (KW < 0) {
+    tm = KW == kRowStrip ? bid : wave;
+    tn = KW == kRowStrip ? wave : bid;
   } else {
-    tm = (int)blockIdx.x / ntn;
-    tn = (int)blockIdx.x % ntn;
+    tm = bid / ntn;
+    tn = bid % ntn;
   }
+  const bool idle = KW < 0 && (tm >= ntm || tn >= ntn);   // still has to meet the others
   const bool c_lower = p.flags & G_C_LOWER;
   if (KW == 1 && (tm >= ntm || tn >= ntn || (c_lower && tn > tm))) return;
   if (KW > 1 && c_lower && tn > tm) return;
@@ -888,7 +898,7 @@ __global__ __launch_bounds__(256) void gemm_direct_kernel(GemmParams<TIn, TCin, 
   if (p.flags & G_A_LOWER) kend = min(K, r0 + 16);
   if (p.flags & G_A_UPPER) kbeg = min(r0, K) / SK * SK;
   if (p.flags & G_B_LOWER) kbeg = min(c0, K) / SK * SK;
-  int steps = kend > kbeg ? (kend - kbeg + SK - 1) / SK : 0;
+  int steps = kend > kbeg && !idle ? (kend - kbeg + SK - 1) / SK : 0;
   if (KW > 1) {
     const int per = (steps + KW - 1) / KW, first = wave * per;
     kbeg += min(first, steps) * SK;
@@ -970,7 +980,34 @@ __global__ __launch_bounds__(256) void gemm_direct_kernel(GemmParams<TIn, TCin, 
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[0][0][r] += part[w][lane][r];
   }
+  if (KW < 0) {
+    __syncthreads();
+    if (idle) return;
+  }
   gemm_epilogue<TIn, TCin, TCout, TC2, 1, 1, 16, 16>(p, acc, zo, zi, z, 0, r0, c0, 0, 0, g, gi);
+}
+
+template <typename TIn, typename TCin, typename TCout, typename TC2, bool BKMAJOR, bool VEC16,
+          int KW>
+__global__ __launch_bounds__(256) void gemm_direct_kernel(GemmParams<TIn, TCin, TCout, TC2> p) {
+  gemm_direct_tile<TIn, TCin, TCout, TC2, BKMAJOR, VEC16, KW>(p, blockIdx.x, blockIdx.z);
+}
+
+// Two independent products in one launch, the first in workgroups [0, first): chains
+// of small products (a factorization's diagonal block) are bound by the number of
+// launches, 4.6 us each on an idle card and 12 us beside large products.
+template <typename T, bool VEC16, int KW0, int KW1>
+__global__ __launch_bounds__(256) void gemm_direct_pair_kernel(GemmParams<T, T, T, float> p0,
+                                                               GemmParams<T, T, T, float> p1,
+                                                               int first) {
+  const int bid = blockIdx.x;
+  if constexpr (KW0 == KW1) {
+    gemm_direct_tile<T, T, T, float, false, VEC16, KW0>(bid < first ? p0 : p1,
+                                                       bid < first ? bid : bid - first, 0);
+  } else {
+    if (bid < first) gemm_direct_tile<T, T, T, float, false, VEC16, KW0>(p0, bid, 0);
+    else gemm_direct_tile<T, T, T, float, false, VEC16, KW1>(p1, bid - first, 0);
+  }
 }
 
 template <typename TIn, typename TCin, typename TCout, typename TC2,
@@ -979,6 +1016,21 @@ __global__ __launch_bounds__(WGM * WGN * 64, 2)
 void gemm_kernel(GemmParams<TIn, TCin, TCout, TC2> p) {
   gemm_tile<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, MODE, CLOWER>(
       p, blockIdx.z, blockIdx.y, blockIdx.x, gridDim.x);
+}
+
+// As gemm_direct_pair_kernel, in 64 x 64 tiles of aligned operands.
+template <typename T>
+__global__ __launch_bounds__(256, 2) void gemm_pair_kernel(GemmParams<T, T, T, float> p0,
+                                                           GemmParams<T, T, T, float> p1,
+                                                           int first) {
+  const int bid = blockIdx.x;
+  // (two copies of the code: a reference chosen at run time puts both structures into
+  // private memory, 67 us instead of 38 for the panels of 7168 rows)
+  if (bid < first)
+    gemm_tile<T, T, T, float, 64, 64, 2, 2, false, kDma16>(p0, 0, 0, bid, first);
+  else
+    gemm_tile<T, T, T, float, 64, 64, 2, 2, false, kDma16>(p1, 0, 0, bid - first,
+                                                          (int)gridDim.x - first);
 }
 
 // Split-K finish: the fixed-order sum of the ksplit partial products of
@@ -1104,6 +1156,15 @@ inline bool direct_ok(const P& p, int batch) {
   return tiles * steps <= std::min<int64_t>(most, (int64_t)512 * p.K);
 }
 
+// Whether a direct product's operands with contiguous k can be read 16 bytes at a time.
+template <typename TIn, bool BKMAJOR, typename P>
+inline bool direct_vec(const P& p) {
+  constexpr int VEC = 16 / (int)sizeof(TIn);
+  auto al = [](const void* x) { return (reinterpret_cast<uintptr_t>(x) & 15) == 0; };
+  return al(p.A) && p.lda % VEC == 0 && p.sa_o % VEC == 0 && p.sa_i % VEC == 0 &&
+         (!BKMAJOR || (al(p.B) && p.ldb % VEC == 0 && p.sb_o % VEC == 0 && p.sb_i % VEC == 0));
+}
+
 // Launch of gemm_direct_kernel (the caller has checked direct_ok).  K is split
 // over a workgroup's waves unless there are many tiles or hardly any steps.
 template <typename TIn, typename TCin, typename TCout, typename TC2, bool BKMAJOR>
@@ -1115,11 +1176,7 @@ inline hipError_t launch_direct(const GemmParams<TIn, TCin, TCout, TC2>& p, int 
   if (kw == 0)
     kw = (int64_t)ntm * ntn * batch > 2048 || p.K * (int)sizeof(TIn) < 512 ? 1 : 4;
   const dim3 grid(kw == 1 ? ((ntm + 1) / 2) * ((ntn + 1) / 2) : ntm * ntn, 1, (unsigned)batch);
-  constexpr int VEC = 16 / (int)sizeof(TIn);
-  auto al = [](const void* x) { return (reinterpret_cast<uintptr_t>(x) & 15) == 0; };
-  const bool vec = al(p.A) && p.lda % VEC == 0 && p.sa_o % VEC == 0 && p.sa_i % VEC == 0 &&
-                   (!BKMAJOR || (al(p.B) && p.ldb % VEC == 0 && p.sb_o % VEC == 0 &&
-                                 p.sb_i % VEC == 0));
+  const bool vec = direct_vec<TIn, BKMAJOR>(p);
   auto go = [&](auto kernel) { kernel<<<grid, 256, 0, stream>>>(q); };
   if (kw == 1) {
     if (vec) go(gemm_direct_kernel<TIn, TCin, TCout, TC2, BKMAJOR, true, 1>);
@@ -1231,6 +1288,52 @@ inline GemmParams<TIn, TCin, TCout, TC2> gemm_params() {
   p.beta = 0.0;
   p.c2scale = 1.0f;
   return p;
+}
+
+// Two independent products without a split, in one launch where both have the same
+// form (small: 16 x 16 tiles; else 64 x 64 tiles of aligned operands) and otherwise one
+// after the other.
+template <typename T>
+inline hipError_t launch_pair(const GemmParams<T, T, T, float>& p0,
+                              const GemmParams<T, T, T, float>& p1, hipStream_t stream) {
+  const bool same = p0.M > 0 && p0.N > 0 && p1.M > 0 && p1.N > 0;
+  if (same && direct_ok<T>(p0, 1) && direct_ok<T>(p1, 1)) {
+    auto tiles = [](const auto& p) { return ((p.M + 15) / 16) * ((p.N + 15) / 16); };
+    const int n0 = tiles(p0), n1 = tiles(p1);
+    const dim3 grid((unsigned)(n0 + n1));
+    if (direct_vec<T, false>(p0) && direct_vec<T, false>(p1))
+      gemm_direct_pair_kernel<T, true, 4, 4><<<grid, 256, 0, stream>>>(p0, p1, n0);
+    else
+      gemm_direct_pair_kernel<T, false, 4, 4><<<grid, 256, 0, stream>>>(p0, p1, n0);
+    return hipGetLastError();
+  }
+  if (same && gemm_mode<T, 64, 64, false>(p0) == kDma16 &&
+      gemm_mode<T, 64, 64, false>(p1) == kDma16) {
+    GemmParams<T, T, T, float> q0 = p0, q1 = p1;
+    q0.ksplit = q1.ksplit = 1;
+    const int n0 = gemm_wgs(p0.M, p0.N, p0.K, p0.flags, 64, 64);
+    const int n1 = gemm_wgs(p1.M, p1.N, p1.K, p1.flags, 64, 64);
+    gemm_pair_kernel<T><<<(unsigned)(n0 + n1), 256, 0, stream>>>(q0, q1, n0);
+    return hipGetLastError();
+  }
+  hipError_t e = launch_gemm<T, T, T, float, 64, 64, 2, 2, false>(p0, 1, stream);
+  return e != hipSuccess ? e : launch_gemm<T, T, T, float, 64, 64, 2, 2, false>(p1, 1, stream);
+}
+
+// X = X B (at most 64 columns, p0: C = A) and Y = A Y (at most 64 rows, p1: C = B) in
+// one launch.
+template <typename T>
+inline hipError_t launch_strips(const GemmParams<T, T, T, float>& p0,
+                                const GemmParams<T, T, T, float>& p1, hipStream_t stream) {
+  if (p0.N > 64 || p1.M > 64) return hipErrorInvalidValue;
+  const int n0 = (p0.M + 15) / 16, n1 = (p1.N + 15) / 16;
+  if (n0 + n1 == 0) return hipSuccess;
+  const dim3 grid((unsigned)(n0 + n1));
+  if (direct_vec<T, false>(p0) && direct_vec<T, false>(p1))
+    gemm_direct_pair_kernel<T, true, kRowStrip, kColStrip><<<grid, 256, 0, stream>>>(p0, p1, n0);
+  else
+    gemm_direct_pair_kernel<T, false, kRowStrip, kColStrip><<<grid, 256, 0, stream>>>(p0, p1, n0);
+  return hipGetLastError();
 }
 
 }  // namespace trsm

@@ -117,6 +117,26 @@ def test_leaf_tiles(torch, T, n, scale):
         assert f.check() == (T.ESINGULAR, bad)
 
 
+@pytest.mark.parametrize("pad", [0, 1])
+@pytest.mark.parametrize("n,nb", [(65, 128), (66, 128), (79, 128), (81, 128), (127, 128),
+                                  (129, 256), (193, 256), (255, 256), (257, 128), (260, 128)])
+def test_paired_products_at_tile_edges(torch, T, n, nb, pad):
+    # inside a block the products that do not depend on each other share a launch
+    # (in place up to 64 columns and rows), and so do a block's two panels: the
+    # second half one short of, at and one past a tile, aligned rows and not
+    A = gen.diag_dominant(n, 13 * n)
+    L, U, full, f = gpu_lu(torch, T, A, nb, lda=n + n % 2 + pad)
+    assert f.check() == (T.OK, -1)
+    Lr, Ur, _ = oracle.lu_nopiv(A)
+    assert oracle.rel_fro_err(L, Lr) <= TOL64 and oracle.rel_fro_err(U, Ur) <= TOL64
+    assert np.all(full[:, n:] == 7.0)
+    s = min(n, nb)
+    VL, VU = f.linv_blocks().cpu().numpy()[0], f.uinv_blocks().cpu().numpy()[0]
+    iu = oracle.inv_lower(np.ascontiguousarray(Ur[:s, :s].T)).T
+    assert oracle.rel_fro_err(VL[:s, :s], oracle.inv_lower(Lr[:s, :s])) <= TOL64
+    assert oracle.rel_fro_err(VU[:s, :s], iu) <= TOL64
+
+
 @pytest.mark.parametrize("n,nb,bad", [(50, 0, 17), (300, 64, 0), (300, 64, 200),
                                       (1000, 256, 999), (1000, 256, 512)])
 def test_bad_pivot_reports_the_row(torch, T, n, nb, bad):
