@@ -192,14 +192,19 @@ __device__ __forceinline__ int col_shift(unsigned bits, int b) {
 // 16 g .. 16 g + 15 of its column to integers, writes the exact binary32 value
 // of the rounded piece (Yq = q 2^-t) back, and stores the residues of four
 // rows as one 32-bit word in LDS; the words then leave as 16-byte pieces of
-// the transposed planes (row c of a plane holds column c of Y).
+// the transposed planes (row c of a plane holds column c of Y).  kYGroup planes
+// at a time: all of them at once take 70 KB, so that two workgroups fill a compute
+// unit and its loads and stores wait for each other (8192 x 8192, ten planes, 1.2 GB:
+// 576 us, now 386).
+constexpr int kYGroup = 4;
+
 __global__ __launch_bounds__(256) void y_residues_kernel(float* __restrict__ Y, int64_t ldy,
                                                           int64_t n, int64_t k,
                                                           const unsigned* __restrict__ colmax,
                                                           int b, Table t,
                                                           int8_t* __restrict__ planes, int64_t ldq,
                                                           int64_t plane, int* __restrict__ ty) {
-  __shared__ uint32_t tile[kPlanes][64][17];
+  __shared__ uint32_t tile[kYGroup][64][17];
   const int tid = threadIdx.x;
   const int64_t i0 = (int64_t)blockIdx.y * 64, c0 = (int64_t)blockIdx.x * 64;
   const int cl = tid & 63, g = tid >> 6;
@@ -217,32 +222,37 @@ __global__ __launch_bounds__(256) void y_residues_kernel(float* __restrict__ Y, 
     const int64_t i = i0 + 16 * g + r;
     if (i < n && c < k) Y[i * ldy + c] = ldexpf((float)q[r], -sh);
   }
-#pragma unroll
-  for (int p = 0; p < kPlanes; ++p) {
-    if (p >= t.P) break;
-    const int m = t.mod[p];
-    const float inv = t.inv[p];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      uint32_t word = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        word |= (uint32_t)(uint8_t)(int8_t)sym_mod_i(q[4 * w + e], m, inv) << (8 * e);
-      tile[p][cl][4 * g + w] = word;
-    }
-  }
-  __syncthreads();
   // thread -> column row (tid >> 2) of the tile, 16 bytes (4 words) each
   const int crow = tid >> 2, part = tid & 3;
-  if (c0 + crow < k) {
-    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+  typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+  int8_t* __restrict__ out = planes + (c0 + crow) * ldq + i0 + 16 * part;
+#pragma unroll 1
+  for (int p0 = 0; p0 < t.P; p0 += kYGroup) {
 #pragma unroll
-    for (int p = 0; p < kPlanes; ++p) {
+    for (int u = 0; u < kYGroup; ++u) {
+      const int p = p0 + u;
       if (p >= t.P) break;
-      u4 o = {tile[p][crow][4 * part], tile[p][crow][4 * part + 1], tile[p][crow][4 * part + 2],
-              tile[p][crow][4 * part + 3]};
-      *reinterpret_cast<u4*>(planes + p * plane + (c0 + crow) * ldq + i0 + 16 * part) = o;
+      const int m = t.mod[p];
+      const float inv = t.inv[p];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        uint32_t word = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          word |= (uint32_t)(uint8_t)(int8_t)sym_mod_i(q[4 * w + e], m, inv) << (8 * e);
+        tile[u][cl][4 * g + w] = word;
+      }
     }
+    __syncthreads();
+    if (c0 + crow < k) {
+#pragma unroll
+      for (int u = 0; u < kYGroup; ++u) {
+        if (p0 + u >= t.P) break;
+        const uint32_t* x = &tile[u][crow][4 * part];
+        *reinterpret_cast<u4*>(out + (p0 + u) * plane) = u4{x[0], x[1], x[2], x[3]};
+      }
+    }
+    __syncthreads();   // before the next planes overwrite the words
   }
 }
 
@@ -380,20 +390,36 @@ __global__ __launch_bounds__(256) void recombine_kernel(
   }
 }
 
-__global__ __launch_bounds__(64) void recombine_final_kernel(const double* __restrict__ part,
+// The blocks' partials, summed in a fixed tree: thread t takes blocks t, t + 256, ...
+// (one lane adding 1024 of them, a load's latency each, took 219 us).
+__global__ __launch_bounds__(256) void recombine_final_kernel(const double* __restrict__ part,
                                                               int blocks, double* __restrict__ out) {
-  if (threadIdx.x != 0) return;
   double r2 = 0.0, rmax = 0.0, x2 = 0.0, xmax = 0.0;
-  for (int b = 0; b < blocks; ++b) {
+  for (int b = threadIdx.x; b < blocks; b += 256) {
     r2 += part[4 * b];
     rmax = fmax(rmax, part[4 * b + 1]);
     x2 += part[4 * b + 2];
     xmax = fmax(xmax, part[4 * b + 3]);
   }
-  out[0] = r2;
-  out[1] = rmax;
-  out[2] = x2;
-  out[3] = xmax;
+  r2 = warp_sum(r2);
+  x2 = warp_sum(x2);
+  rmax = warp_max(rmax);
+  xmax = warp_max(xmax);
+  __shared__ double sm[4][4];
+  if ((threadIdx.x & 63) == 0) {
+    double* w = sm[threadIdx.x >> 6];
+    w[0] = r2;
+    w[1] = rmax;
+    w[2] = x2;
+    w[3] = xmax;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    out[0] = sm[0][0] + sm[1][0] + sm[2][0] + sm[3][0];
+    out[1] = fmax(fmax(sm[0][1], sm[1][1]), fmax(sm[2][1], sm[3][1]));
+    out[2] = sm[0][2] + sm[1][2] + sm[2][2] + sm[3][2];
+    out[3] = fmax(fmax(sm[0][3], sm[1][3]), fmax(sm[2][3], sm[3][3]));
+  }
 }
 
 }  // namespace
@@ -484,7 +510,7 @@ hipError_t launch_recombine(const int8_t* Z, int64_t ldz, int64_t zplane, const 
                             hipStream_t s) {
   recombine_kernel<<<kRecBlocks, 256, 0, s>>>(Z, ldz, zplane, t, sl, ty, Yq, ldy, yshift, L, ldl,
                                               Rin, ldri, Rout, ldro, Rl, X, ldx, xmode, n, k, part);
-  recombine_final_kernel<<<1, 64, 0, s>>>(part, kRecBlocks, out);
+  recombine_final_kernel<<<1, 256, 0, s>>>(part, kRecBlocks, out);
   return hipGetLastError();
 }
 

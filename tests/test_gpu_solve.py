@@ -322,6 +322,18 @@ def test_mixed_refined(torch, T, prec, n, k, n0):
     assert err0 <= (1e-1 if prec == "fp8" else 1e-2)
 
 
+@pytest.mark.parametrize("k", [1, 3, 37, 63, 66, 261, 1026])
+def test_mixed_ragged_columns(torch, T, k):
+    # the passes over the right-hand sides read 16 or 4 bytes a lane by k, and
+    # their last loads of a row fall inside it: same bound as above
+    L, B = gen.easy_system(300, k, 51 + k, upper=np.nan)
+    B[17, k - 1] = 1000.0   # the largest element in the last column
+    info = T.Info()
+    X = gpu_solve(torch, T, L, B, precision="f16", n0=64, info=info)
+    assert info.converged == 1
+    assert oracle.rel_fro_err(X, oracle.trsm(L, B)) <= TOL64
+
+
 @pytest.mark.parametrize("prec", ["bf16", "f16", "fp8"])
 def test_mixed_hard_matrix(torch, T, prec):
     # |X| reaches ~1e5 |B| here, beyond half's range unless the low copy of
