@@ -479,9 +479,9 @@ constexpr unsigned kSpinLimit = 1u << 22;
 constexpr int kPassBlocks = 4;
 
 template <typename T, bool ALIGNED>
-__device__ __forceinline__ void persist_tile(const GemmParams<T, T, T, float>& p) {
+__device__ __forceinline__ void persist_tile(const GemmParams<T, T, T, float>& p, char* smem) {
   if constexpr (ALIGNED)
-    gemm_tile_dma<T, T, T, float, kPB, kPB, 2, 2>(p, 0, 0, 0, 0);
+    gemm_tile_dma<T, T, T, float, kPB, kPB, 2, 2>(p, 0, 0, 0, 0, smem);
   else
     gemm_tile_staged<T, T, T, float, kPB, kPB, 2, 2, false, false>(p, 0, 0, 0, 0);
 }
@@ -512,6 +512,7 @@ __global__ __launch_bounds__(256, 2) void persist_sweep_kernel(
     const PersistItem<T>* __restrict__ items, const PersistTask* __restrict__ tasks, int ntasks,
     unsigned* __restrict__ cnt, int ncnt) {
   __shared__ int s_task;
+  __shared__ __attribute__((aligned(1024))) char smem[ALIGNED ? dma_lds<T, kPB, kPB, false>() : 16];
   unsigned* head = cnt + ncnt;
   unsigned* err = cnt + ncnt + 1;
   for (;;) {
@@ -552,7 +553,7 @@ __global__ __launch_bounds__(256, 2) void persist_sweep_kernel(
       p.M = sz; p.N = nc; p.K = (avail - done) * nb;
       p.alpha = -1.0; p.beta = 1.0;
       p.flags = G_BETA;
-      persist_tile<T, ALIGNED>(p);
+      persist_tile<T, ALIGNED>(p, smem);
       done = avail;
       __threadfence();
       __syncthreads();
@@ -565,7 +566,7 @@ __global__ __launch_bounds__(256, 2) void persist_sweep_kernel(
       p.Cout = it.X + (int64_t)r0 * it.ldx + c0; p.ldco = it.ldx;
       p.M = sz; p.N = nc; p.K = sz;
       p.flags = G_A_LOWER | G_A_ZERO_UPPER;
-      persist_tile<T, ALIGNED>(p);
+      persist_tile<T, ALIGNED>(p, smem);
     }
     __threadfence();   // release: X(S_i, c) is visible before the counter moves
     __syncthreads();
@@ -589,32 +590,54 @@ hipError_t launch_persist(const void* items, const void* tasks, int ntasks, unsi
   return hipGetLastError();
 }
 
-template <typename T, int BM, int BN, int WGM, int WGN, int MODE>
-void launch_grouped_as(const GemmParams<T, T, T, float>* e, const int* start, int count, dim3 grid,
-                       hipStream_t s) {
-  gemm_grouped_kernel<T, T, T, float, BM, BN, WGM, WGN, false, MODE><<<grid, 256, 0, s>>>(e, start,
-                                                                                         count);
+// Grouped products of 128 x 32 and 64 x 64 tiles with any of the three ways to LDS, in
+// one launch: entry e's form (tile shape and GemmMode) is start[n + 1 + e].  Such
+// launches are short and bound by the chain of their longest entry, so one for
+// each form would add up those chains (48 uneven systems in binary32: 187 us in four
+// launches a phase, 80 in one).
+constexpr int form_of(int shape, int mode) { return shape * (kDma16 + 1) + mode; }
+
+template <typename T>
+__global__ __launch_bounds__(256, 2) void gemm_forms_kernel(
+    const GemmParams<T, T, T, float>* __restrict__ entries, const int* __restrict__ start, int n) {
+  constexpr int kNarrowLds = dma_lds<T, kBM, kNarrowN, false>();
+  constexpr int kMidLds = dma_lds<T, kMidTile, kMidTile, false>();
+  __shared__ __attribute__((aligned(1024))) char smem[kNarrowLds > kMidLds ? kNarrowLds : kMidLds];
+  const int lo = owner_of(start, n, blockIdx.x);
+  const GemmParams<T, T, T, float>& p = entries[lo];
+  const int local = (int)blockIdx.x - start[lo];
+  auto narrow = [&](auto mode) {
+    const int tiles = gemm_wgs(p.M, p.N, p.K, p.flags, kBM, kNarrowN);
+    gemm_tile<T, T, T, float, kBM, kNarrowN, 4, 1, false, mode()>(p, 0, local / tiles,
+                                                                 local % tiles, tiles, smem);
+  };
+  auto mid = [&](auto mode) {
+    const int tiles = gemm_wgs(p.M, p.N, p.K, p.flags, kMidTile, kMidTile);
+    gemm_tile<T, T, T, float, kMidTile, kMidTile, 2, 2, false, mode()>(p, 0, local / tiles,
+                                                                      local % tiles, tiles, smem);
+  };
+  switch (__builtin_amdgcn_readfirstlane(start[n + 1 + lo])) {
+    case form_of(kNarrow, kDma4): narrow(std::integral_constant<int, kDma4>()); break;
+    case form_of(kNarrow, kDma16A): narrow(std::integral_constant<int, kDma16A>()); break;
+    case form_of(kNarrow, kDma16): narrow(std::integral_constant<int, kDma16>()); break;
+    case form_of(kMid, kDma4): mid(std::integral_constant<int, kDma4>()); break;
+    case form_of(kMid, kDma16A): mid(std::integral_constant<int, kDma16A>()); break;
+    case form_of(kMid, kDma16): mid(std::integral_constant<int, kDma16>()); break;
+  }
 }
 
-// One grouped launch of products that share a tile shape and a mode.
+// One grouped launch.
 template <typename T>
 void launch_grouped(const GemmParams<T, T, T, float>* e, const int* start, int count, int shape,
                     int mode, dim3 grid, hipStream_t s) {
-  auto pick = [&](auto by16, auto by16a, auto by4) {
-    (mode == kDma16 ? by16 : mode == kDma16A ? by16a : by4)(e, start, count, grid, s);
-  };
-  if (shape == kNarrow)
-    pick(launch_grouped_as<T, kBM, kNarrowN, 4, 1, kDma16>,
-         launch_grouped_as<T, kBM, kNarrowN, 4, 1, kDma16A>,
-         launch_grouped_as<T, kBM, kNarrowN, 4, 1, kDma4>);
-  else if (shape == kMid)
-    pick(launch_grouped_as<T, kMidTile, kMidTile, 2, 2, kDma16>,
-         launch_grouped_as<T, kMidTile, kMidTile, 2, 2, kDma16A>,
-         launch_grouped_as<T, kMidTile, kMidTile, 2, 2, kDma4>);
+  if (shape != kWide)
+    gemm_forms_kernel<T><<<grid, 256, 0, s>>>(e, start, count);
   else if (mode == kDma16)
-    launch_grouped_as<T, kBM, kBN, 2, 2, kDma16>(e, start, count, grid, s);
+    gemm_grouped_kernel<T, T, T, float, kBM, kBN, 2, 2, false, kDma16>
+        <<<grid, 256, 0, s>>>(e, start, count);
   else
-    launch_grouped_as<T, kBM, kBN, 2, 2, kStaged>(e, start, count, grid, s);
+    gemm_grouped_kernel<T, T, T, float, kBM, kBN, 2, 2, false, kStaged>
+        <<<grid, 256, 0, s>>>(e, start, count);
 }
 
 }  // namespace
@@ -662,10 +685,17 @@ template <typename P>
 void LaunchList::add_gemm(int kind, int split_kind, std::vector<P> entries) {
   if (entries.empty()) return;
   using T = typename std::remove_const<typename std::remove_pointer<decltype(P::A)>::type>::type;
-  // sub-launches by tile shape and by how the operands reach LDS; both follow from
-  // the entry alone, so its tiles and sums do not depend on the others
-  std::vector<P> sub[kShapes][kDma16 + 1];
+  // Tile shape and way to LDS follow from the entry alone, so its tiles and sums do not
+  // depend on the others.  Sub-launches: all entries of small tiles, 128 x 128
+  // tiles of aligned operands, the rest.
+  struct Sub {
+    std::vector<P> e;
+    std::vector<int> form;
+  } sub[3];
   std::vector<P> split;
+  // the longest chains first: a launch ends with its last one
+  std::stable_sort(entries.begin(), entries.end(),
+                   [](const P& a, const P& b) { return a.K > b.K; });
   for (P& e : entries) {
     e.ksplit = grouped_ksplit<T>(e);
     if (e.ksplit > 1) split.push_back(e);
@@ -677,27 +707,32 @@ void LaunchList::add_gemm(int kind, int split_kind, std::vector<P> entries) {
                gemm_wgs(e.M, e.N, e.K, e.flags, kBM, kBN) * e.ksplit < kWideFrom)
         shape = kMid;
     }
-    sub[shape][mode].push_back(e);
+    Sub& b = sub[shape != kWide ? 0 : mode == kDma16 ? 1 : 2];
+    b.e.push_back(e);
+    b.form.push_back(form_of(shape, mode));
   }
-  for (int shape = 0; shape < kShapes; ++shape)
-    for (int mode = 0; mode <= kDma16; ++mode) {
-      const std::vector<P>& v = sub[shape][mode];
-      if (v.empty()) continue;
-      Phase ph{};
-      ph.kind = kind;
-      ph.count = (int)v.size();
-      ph.shape = shape;
-      ph.mode = mode;
+  for (const Sub& b : sub) {
+    const int count = (int)b.e.size();
+    if (!count) continue;
+    Phase ph{};
+    ph.kind = kind;
+    ph.count = count;
+    std::vector<int> st(count + 1, 0);
+    for (int i = 0; i < count; ++i) {
+      const P& e = b.e[i];
+      const int shape = b.form[i] / (kDma16 + 1);
       const int bm = shape == kMid ? kMidTile : kBM;
       const int bn = shape == kMid ? kMidTile : shape == kNarrow ? kNarrowN : kBN;
-      std::vector<int> st(v.size() + 1, 0);
-      for (size_t i = 0; i < v.size(); ++i)
-        st[i + 1] = st[i] + gemm_wgs(v[i].M, v[i].N, v[i].K, v[i].flags, bm, bn) * v[i].ksplit;
-      ph.total = st.back();
-      ph.entries_off = append(v.data(), v.size());
-      ph.start_off = append(st.data(), st.size());
-      if (ph.total > 0) phases_.push_back(ph);
+      st[i + 1] = st[i] + gemm_wgs(e.M, e.N, e.K, e.flags, bm, bn) * e.ksplit;
+      ph.shape = shape;
+      ph.mode = b.form[i] % (kDma16 + 1);
     }
+    ph.total = st.back();
+    st.insert(st.end(), b.form.begin(), b.form.end());
+    ph.entries_off = append(b.e.data(), b.e.size());
+    ph.start_off = append(st.data(), st.size());
+    if (ph.total > 0) phases_.push_back(ph);
+  }
   if (split.empty()) return;
   Phase fin{};
   fin.kind = split_kind;

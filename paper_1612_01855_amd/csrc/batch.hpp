@@ -154,11 +154,12 @@ class LaunchList {
   struct Phase {
     int kind;
     size_t entries_off;  // byte offset of the entry array in the table
-    size_t start_off;    // byte offset of the int prefix array (n + 1 values); tasks (persistent)
+    size_t start_off;    // byte offset of the int prefix array (n + 1 values; products: then
+                         // the n forms); tasks (persistent)
     int count;
     int total;           // workgroups
     bool aligned;                   // persistent sweep
-    int shape = 0, mode = 0;        // grouped products: tile shape and GemmMode
+    int shape = 0, mode = 0;        // grouped products: tile shape and GemmMode (of 128 x 128)
     unsigned* counters = nullptr;   // persistent: counters, queue head, error word
     int ncounters = 0;
     int ntasks = 0;

@@ -341,6 +341,14 @@ constexpr int vmcnt_imm(int n) {
 // s_waitcnt immediate that waits for every vector-memory and LDS operation.
 constexpr int kWaitAll = 0x7 << 4;
 
+// LDS of gemm_tile_dma: two stages of A's and B's 128 bytes of k (B row-major: 16
+// bytes between the KB that one instruction copies).
+template <typename TIn, int BM, int BN, bool BKMAJOR>
+constexpr int dma_lds() {
+  const int bk = 128 / (int)sizeof(TIn), row_b = BN * (int)sizeof(TIn);
+  return 2 * (BM * 128 + (BKMAJOR ? BN * 128 : bk * row_b / 1024 * (1024 + 16)));
+}
+
 // Matrix-core tile with operands copied from HBM straight into LDS by
 // buffer loads (no register staging), two LDS stages, one barrier per chunk.
 // For one-k-per-lane instructions (binary64, binary32).  A16 / B16: the operand's
@@ -370,7 +378,8 @@ constexpr int kWaitAll = 0x7 << 4;
 template <typename TIn, typename TCin, typename TCout, typename TC2, int BM, int BN, int WGM,
           int WGN, bool BKMAJOR = false, bool A16 = true, bool B16 = true>
 __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout, TC2>& p, int z,
-                                              int s, const int r0, const int c0) {
+                                              int s, const int r0, const int c0,
+                                              char* const smem) {
   using MF = Mfma<TIn>;
   using Acc = typename MF::Acc;
   using Out = typename MF::Out;
@@ -395,7 +404,7 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout,
   static_assert(RPI * ROW_B == 1024, "a wave instruction must cover whole B rows");
   static_assert(A_INST * NW * 8 == BM && B_INST * NW == B_INST_TOTAL, "even split of loads");
   static_assert(!BKMAJOR || BT_INST * NW * 8 == BN, "even split of B^T loads");
-  __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE];
+  static_assert(2 * STAGE == dma_lds<TIn, BM, BN, BKMAJOR>(), "the caller's LDS");
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -811,17 +820,22 @@ __device__ __forceinline__ void gemm_tile_staged(const GemmParams<TIn, TCin, TCo
 
 
 // The output tiles of workgroup `bid` (of nwg) of one batch entry z: one
-// tile, or two for a folded triangular product.
+// tile, or two for a folded triangular product.  smem: tile_lds bytes.
+template <typename TIn, int BM, int BN, bool BKMAJOR, int MODE>
+constexpr int tile_lds() {
+  return MODE != kStaged && Mfma<TIn>::kPerLane == 1 ? dma_lds<TIn, BM, BN, BKMAJOR>() : 16;
+}
+
 template <typename TIn, typename TCin, typename TCout, typename TC2,
           int BM, int BN, int WGM, int WGN, bool BKMAJOR, int MODE, bool CLOWER = false,
           int GROUP_M = 8, bool XCD_REMAP = false>
 __device__ __forceinline__ void gemm_tile(const GemmParams<TIn, TCin, TCout, TC2>& p, int z,
-                                          int s, int bid, int nwg) {
+                                          int s, int bid, int nwg, char* smem) {
   const int ntm = (p.M + BM - 1) / BM, ntn = (p.N + BN - 1) / BN;
   auto one = [&](int tm, int tn) {
     if constexpr (MODE != kStaged && Mfma<TIn>::kPerLane == 1)
       gemm_tile_dma<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, MODE != kDma4, MODE == kDma16>(
-          p, z, s, tm * BM, tn * BN);
+          p, z, s, tm * BM, tn * BN, smem);
     else
       gemm_tile_staged<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, MODE == kDma16>(
           p, z, s, tm * BM, tn * BN);
@@ -1014,8 +1028,9 @@ template <typename TIn, typename TCin, typename TCout, typename TC2,
           int BM, int BN, int WGM, int WGN, bool BKMAJOR, int MODE, bool CLOWER = false>
 __global__ __launch_bounds__(WGM * WGN * 64, 2)
 void gemm_kernel(GemmParams<TIn, TCin, TCout, TC2> p) {
+  __shared__ __attribute__((aligned(1024))) char smem[tile_lds<TIn, BM, BN, BKMAJOR, MODE>()];
   gemm_tile<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, MODE, CLOWER>(
-      p, blockIdx.z, blockIdx.y, blockIdx.x, gridDim.x);
+      p, blockIdx.z, blockIdx.y, blockIdx.x, gridDim.x, smem);
 }
 
 // As gemm_direct_pair_kernel, in 64 x 64 tiles of aligned operands.
@@ -1026,11 +1041,12 @@ __global__ __launch_bounds__(256, 2) void gemm_pair_kernel(GemmParams<T, T, T, f
   const int bid = blockIdx.x;
   // (two copies of the code: a reference chosen at run time puts both structures into
   // private memory, 67 us instead of 38 for the panels of 7168 rows)
+  __shared__ __attribute__((aligned(1024))) char smem[dma_lds<T, 64, 64, false>()];
   if (bid < first)
-    gemm_tile<T, T, T, float, 64, 64, 2, 2, false, kDma16>(p0, 0, 0, bid, first);
+    gemm_tile<T, T, T, float, 64, 64, 2, 2, false, kDma16>(p0, 0, 0, bid, first, smem);
   else
     gemm_tile<T, T, T, float, 64, 64, 2, 2, false, kDma16>(p1, 0, 0, bid - first,
-                                                          (int)gridDim.x - first);
+                                                          (int)gridDim.x - first, smem);
 }
 
 // Split-K finish: the fixed-order sum of the ksplit partial products of
@@ -1082,8 +1098,9 @@ void gemm_grouped_kernel(const GemmParams<TIn, TCin, TCout, TC2>* __restrict__ e
   const GemmParams<TIn, TCin, TCout, TC2>& p = entries[lo];
   const int tiles = gemm_wgs(p.M, p.N, p.K, p.flags, BM, BN);
   const int local = b - tile_start[lo];
+  __shared__ __attribute__((aligned(1024))) char smem[tile_lds<TIn, BM, BN, BKMAJOR, MODE>()];
   gemm_tile<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, MODE>(p, 0, local / tiles,
-                                                                   local % tiles, tiles);
+                                                                   local % tiles, tiles, smem);
 }
 
 // How a product's operands reach LDS.  Binary64/binary32: kDma16 if the rows of both
