@@ -583,8 +583,8 @@ trsm_status trsm_lu_check(const void* workspace, trsm_status* status, int64_t* i
  * dgetrf's exchanges).  Built on the triangular solve of Alg. It-Inv-TRSM
  * (the abstract and Sec. I name LU as built on TRSM): block columns of nb
  * (a power of two >= 32) are factored in 32-column panels (one launch per
- * panel; above 1024 rows a cooperative one with one device-wide meeting per
- * column); then each block's
+ * panel; above 1024 rows of several workgroups that meet once per column,
+ * cooperative above 4096); then each block's
  * unit lower diagonal block is inverted by Alg. Diagonal-Inverter +
  * RecTriInv, U(S_j, T_j) = Linv_jj A(S_j, T_j) is one product with the
  * inverted block, and A(T_j, T_j) -= L(T_j, S_j) U(S_j, T_j).  n <= 65536.
@@ -612,8 +612,8 @@ trsm_status trsm_lu_check(const void* workspace, trsm_status* status, int64_t* i
  * trsm_lu_piv_check(workspace, &status, &index): blocking.  TRSM_OK and -1;
  *  TRSM_ESINGULAR and the first column whose pivot was zero or not finite
  *  (the factorization goes on, as LAPACK does, and U is singular); or
- *  TRSM_EHIP and -1 if a panel's wait gave up (ruled out by the
- *  cooperative launch; reported rather than hung).
+ *  TRSM_EHIP and -1 if a panel's wait gave up (its workgroups could not run
+ *  at once for seconds on end; reported rather than hung).
  * trsm_row_swaps(k0, k1, ipiv, B, ldb, ncols, stream): applies "swap rows k
  *  and ipiv[k]" for k = k0 .. k1-1 in order to the first ncols columns of the
  *  device matrix B (row-major, ldb >= ncols): P B for a factorization's

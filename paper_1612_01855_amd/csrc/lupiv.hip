@@ -21,7 +21,7 @@
 // The panel kernel keeps the panel in registers (one or two rows per thread).
 // A panel of at most 1024 rows is one workgroup and needs no device-wide
 // meeting; taller ones run on G co-resident workgroups
-// (cooperative launch) that meet once per column: every workgroup publishes
+// (launch_panel) that meet once per column: every workgroup publishes
 // its best candidate (largest magnitude, the first position on ties, positions
 // being the row order after the exchanges so far) together with that row's
 // values, each picks the winner from the G candidates and eliminates its own
@@ -584,6 +584,17 @@ hipError_t prod(const double* A, int64_t lda, const double* B, int64_t ldb, doub
 // (no meeting); then one row per thread while every wave has at most one
 // candidate to wait for, because a step's update and LDS traffic grow with
 // the rows per thread; two beyond that, to bound the candidates to read.
+//
+// Several workgroups wait for each other, so all of them have to run at once.  Up to
+// kPlainGroups of one row per thread they are launched like any other kernel: every
+// kernel beside them ends by itself, and those that wait in the same way (one for
+// each hardware queue of each process on the card, 16 processes of 4) need no more
+// than the two places that each of the 256 compute units has for such workgroups (116
+// registers, 8 waves); a wait that lasts all the same ends at kSpinLimit with the error
+// word set.  A cooperative launch idles about 11 us before and after it (n = 4096, 96
+// panels of 82 us: 15.7 ms with it, 13.8 without) and remains for more workgroups.
+constexpr int64_t kPlainGroups = kWaves;
+
 template <int RPT, bool MULTI>
 hipError_t launch_panel(double* A, int64_t lda, int64_t c, int h, int w, int64_t* ipiv,
                         unsigned long long* slots, Words* words, Moves* mv, hipStream_t s) {
@@ -591,11 +602,17 @@ hipError_t launch_panel(double* A, int64_t lda, int64_t c, int h, int w, int64_t
     piv_panel_kernel<RPT, false><<<1, kThreads, 0, s>>>(A, lda, c, c, h, w, ipiv, slots, words, mv);
     return hipGetLastError();
   } else {
+    const int64_t groups = ceil_div(h, kThreads * RPT);
+    if (RPT == 1 && groups <= kPlainGroups) {
+      piv_panel_kernel<RPT, true><<<(unsigned)groups, kThreads, 0, s>>>(A, lda, c, c, h, w, ipiv,
+                                                                       slots, words, mv);
+      return hipGetLastError();
+    }
     int64_t r0 = c, cc = c;
     void* args[] = {&A, &lda, &r0, &cc, &h, &w, &ipiv, &slots, &words, &mv};
     return hipLaunchCooperativeKernel(
         reinterpret_cast<const void*>(piv_panel_kernel<RPT, true>),
-        dim3((unsigned)ceil_div(h, kThreads * RPT)), dim3(kThreads), args, 0, s);
+        dim3((unsigned)groups), dim3(kThreads), args, 0, s);
   }
 }
 
