@@ -408,7 +408,7 @@ __global__ __launch_bounds__(kThreads) void piv_panel_kernel(
 // the (at most 2 w) rows the panel moved -- all loads before the first store
 // -- and for those columns solves with the panel's unit lower triangle (x_i =
 // b_i - sum_{p<i} l_ip x_p, i and p ascending) before it writes them.  One
-// pass over at most 2 w rows of the matrix: 19 us at n = 4096; exchanging the
+// pass over at most 2 w rows of the matrix: 16 us at n = 4096; exchanging the
 // rows one pair at a time was a chain of w dependent memory round trips (1 to
 // 1.5 us each), once for the block's columns and once for all others.
 constexpr int kMoveCols = 64;
