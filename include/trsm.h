@@ -81,8 +81,9 @@ typedef enum trsm_precision {
                                        nor with TRSM_FLAG_TRANSPOSE, TRSM_FLAG_RECURSIVE or
                                        TRSM_FLAG_LOOKAHEAD (trsm_plan: TRSM_EINVAL) */
 #define TRSM_FLAG_LARGE_TILES 0x8u  /* every product uses 128 x 128 tiles and an unsplit
-                                       reduction (default: products with few tiles use 64 x 64
-                                       tiles and split K); one of the tile policies
+                                       reduction (64 x 64 where operands are not 16-byte
+                                       aligned; default: products with few tiles or a short
+                                       K use 64 x 64 tiles and split K); one of the policies
                                        trsm_autotune chooses between */
 
 typedef struct trsm_plan_s* trsm_plan_t;

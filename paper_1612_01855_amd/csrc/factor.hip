@@ -108,7 +108,9 @@ __global__ __launch_bounds__(kCholThreads<NT>, 4) void chol_leaf_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   __builtin_amdgcn_s_setprio(3);   // before the trailing products' waves beside it
   const int nt = (s + 15) >> 4;
-  auto at = [&](int r, int c) { return Map::at(S, r >> 4, min(c >> 4, r >> 4)) + (r & 15) * kTld + (c & 15); };
+  auto at = [&](int r, int c) {
+    return Map::at(S, r >> 4, min(c >> 4, r >> 4)) + (r & 15) * kTld + (c & 15);
+  };
   double v[C::kEach];
   C().each(ldd, [&](int r, int c, int q, int64_t o) { v[q] = D[r < s && c <= r ? o : 0]; });
   int first = C::kRows;
@@ -335,8 +337,9 @@ hipError_t prod(const Ctx& c, const double* A, int64_t lda, const double* B, int
                 double* C, int64_t ldc, int64_t M, int64_t N, int64_t K, double alpha,
                 bool accumulate, uint32_t flags, bool split = true) {
   const auto p = prod_params(c, A, lda, B, ldb, C, ldc, M, N, K, alpha, accumulate, flags, split);
-  return small_tile<double>(p, 1) ? launch_gemm<double, double, double, float, 64, 64, 2, 2, BT>(p, 1, c.s)
-                                  : launch_gemm<double, double, double, float, 128, 128, 2, 2, BT>(p, 1, c.s);
+  return small_tile<double>(p, 1)
+             ? launch_gemm<double, double, double, float, 64, 64, 2, 2, BT>(p, 1, c.s)
+             : launch_gemm<double, double, double, float, 128, 128, 2, 2, BT>(p, 1, c.s);
 }
 
 #define CHOL_HIP(...)                                           \
@@ -581,8 +584,8 @@ trsm_status lu_init(const Ctx& c, int64_t m) {
 }
 
 // The panels L(T_j, S_j) = A(T_j, S_j) Uinv_jj into PL (ld nb) and U(S_j, T_j) =
-// Linv_jj A(S_j, T_j) into PU (ld n - nb): t rows and columns, in one launch.  7168 rows and columns, K = 256:
-// 38 us, one after the other 50.
+// Linv_jj A(S_j, T_j) into PU (ld n - nb): t rows and columns, in one launch.  7168 rows
+// and columns, K = 256: 38 us, one after the other 50.
 trsm_status lu_panels(const Ctx& c, const double* A21, const double* A12, const double* VL,
                       const double* VU, double* PL, double* PU, int64_t s, int64_t t) {
   const int64_t nb = c.nb, ldu = c.n - nb;

@@ -576,8 +576,9 @@ hipError_t prod(const double* A, int64_t lda, const double* B, int64_t ldb, doub
   p.flags = flags;
   p.part = split;
   p.part_bytes = (int64_t)split_bytes;
-  return small_tile<double>(p, 1) ? launch_gemm<double, double, double, float, 64, 64, 2, 2, false>(p, 1, s)
-                                  : launch_gemm<double, double, double, float, 128, 128, 2, 2, false>(p, 1, s);
+  return small_tile<double>(p, 1)
+             ? launch_gemm<double, double, double, float, 64, 64, 2, 2, false>(p, 1, s)
+             : launch_gemm<double, double, double, float, 128, 128, 2, 2, false>(p, 1, s);
 }
 
 // One panel.  Rows per thread and workgroups: one workgroup while the rows fit

@@ -134,7 +134,7 @@ struct SplitBuf {
 };
 thread_local SplitBuf g_split;
 
-// Tile policy of the current call (TRSM_FLAG_LARGE_TILES: 128 x 128 only).
+// Tile policy of the current call (TRSM_FLAG_LARGE_TILES: 128 x 128 where aligned).
 thread_local bool g_large_tiles = false;
 
 struct TilePolicyScope {
