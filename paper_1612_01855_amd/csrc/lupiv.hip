@@ -39,11 +39,11 @@
 #include "common.hpp"
 #include "gemm.hpp"
 #include "kernels.hpp"
+#include "panel.hpp"
 
 namespace trsm {
 namespace {
 
-constexpr int kPw = 32;               // panel width
 constexpr int kSub = 8;               // columns per unrolled group of steps
 constexpr int kThreads = 512;         // threads per panel workgroup
 constexpr int kWaves = kThreads / 64;
@@ -62,14 +62,6 @@ struct Words {
   unsigned long long bad;   // smallest column with a zero or non-finite pivot
   unsigned unused;
   unsigned err;             // a wait for a candidate gave up
-};
-
-// Where the rows a panel exchanged came from and went to (panel-relative):
-// the row at position i < w after the panel was row src[i] before it, and the
-// row that was at i is at dst[i] now.
-struct Moves {
-  int src[kPw];
-  int dst[kPw];
 };
 
 // Rank of a row in the pivot search, as an integer so that the largest
@@ -313,13 +305,9 @@ __global__ __launch_bounds__(kThreads) void piv_panel_kernel(
           blo = (unsigned)__builtin_amdgcn_readlane((int)k.lo, sw);
           p = __builtin_amdgcn_readlane(k.pos, sw);
           u = grow[par][sw][lane & (kPw - 1)];
-          // a position outside j .. h-1 can only come from candidates read
-          // after a wait gave up (reported through the error word): fall back
-          // to j so that every row still goes back to a row of the panel
-          if (p < j || p >= h) {
-            p = j;
-            if (tid == 0) atomicOr(&words->err, 2u);
-          }
+          const int chosen = pivot_position(p, j, h);
+          if (chosen != p && tid == 0) atomicOr(&words->err, 2u);
+          p = chosen;
         }
         const unsigned long long rank = (unsigned long long)bhi << 32 | blo;
         // a zero, infinite or NaN pivot: ranks 2, of infinity, and below 2
@@ -424,9 +412,11 @@ __global__ __launch_bounds__(kMoveCols) void panel_apply_kernel(double* __restri
   const bool inside = live && col >= c0 + w && col < e0;
   const bool any = __any(inside);
   double* __restrict__ P = A + c0 * lda + (live ? col : 0);
+  const int h = (int)(n - c0);
   double x[kPw], y[kPw];
 #pragma unroll
-  for (int i = 0; i < kPw; ++i) x[i] = i < w ? P[(int64_t)mv->src[i] * lda] : 0.0;
+  for (int i = 0; i < kPw; ++i)
+    x[i] = i < w ? P[(int64_t)moved_row(mv->src[i], i, h) * lda] : 0.0;
 #pragma unroll
   for (int i = 0; i < kPw; ++i) y[i] = i < w ? P[(int64_t)i * lda] : 0.0;
   if (any) {
@@ -456,7 +446,7 @@ __global__ __launch_bounds__(kMoveCols) void panel_apply_kernel(double* __restri
   for (int i = 0; i < kPw; ++i)
     if (i < w) {
       if (inside || mv->src[i] != i) P[(int64_t)i * lda] = x[i];
-      const int d = mv->dst[i];
+      const int d = moved_row(mv->dst[i], i, h);
       if (d >= w) P[(int64_t)d * lda] = y[i];
     }
 }
