@@ -585,7 +585,8 @@ trsm_status trsm_lu_check(const void* workspace, trsm_status* status, int64_t* i
  * (the abstract and Sec. I name LU as built on TRSM): block columns of nb
  * (a power of two >= 32) are factored in 32-column panels (one launch per
  * panel; above 1024 rows of several workgroups that meet once per column,
- * cooperative above 4096); then each block's
+ * cooperative above 4096, or above 1024 on partitions too small for several
+ * such panels at once); then each block's
  * unit lower diagonal block is inverted by Alg. Diagonal-Inverter +
  * RecTriInv, U(S_j, T_j) = Linv_jj A(S_j, T_j) is one product with the
  * inverted block, and A(T_j, T_j) -= L(T_j, S_j) U(S_j, T_j).  n <= 65536.

@@ -34,6 +34,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <atomic>
 
 #include "../../include/trsm.h"
 #include "common.hpp"
@@ -45,14 +46,15 @@ namespace trsm {
 namespace {
 
 constexpr int kSub = 8;               // columns per unrolled group of steps
-constexpr int kThreads = 512;         // threads per panel workgroup
+constexpr int kThreads = kPanelThreads;
 constexpr int kWaves = kThreads / 64;
-constexpr int kMaxRpt = 2;            // panel rows per thread: 1 or 2
-constexpr int64_t kMaxN = 65536;      // rows a panel may have (positions fit a slot's tags)
-constexpr int kMaxGroups = (int)(kMaxN / (kThreads * kMaxRpt));   // workgroups of a panel
+constexpr int64_t kMaxN = kMaxPanelRows;
 constexpr int kSlotWords = 2 * kPw;   // 8-byte words of a candidate slot
 constexpr int kNoPos = (1 << 20) - 1; // position of "no candidate" (times kWaves fits an int)
-constexpr unsigned kSpinLimit = 1u << 22;
+// Polls of a wait before it gives up, about a microsecond each (more than ten
+// seconds in all); after kSpinBusy of them the wave sleeps between two.
+constexpr unsigned kSpinLimit = 1u << 24;
+constexpr unsigned kSpinBusy = 1u << 10;
 constexpr size_t kAl = 256;
 constexpr size_t kSplitBytes = (size_t)32 << 20;
 inline size_t al(size_t v) { return (v + kAl - 1) / kAl * kAl; }
@@ -223,7 +225,8 @@ __global__ __launch_bounds__(kThreads) void piv_panel_kernel(
     for (int r = 0; r < RPT; ++r) x[r] = a[r][0];
     search(x);
   }
-  bool dead = false;                      // a wait gave up: later ones do not wait
+  // a wait gave up, here or in an earlier panel: later ones do not wait
+  bool dead = MULTI && __hip_atomic_load(&words->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   for (int q = 0; q < kPw / kSub; ++q) {
 #pragma unroll
     for (int jj = 0; jj < kSub; ++jj) {
@@ -278,7 +281,8 @@ __global__ __launch_bounds__(kThreads) void piv_panel_kernel(
                 __hip_atomic_load(sl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             unsigned spins = 0;
             while (!dead && __any((unsigned)(word >> 47) != step)) {
-              if (++spins > kSpinLimit) {
+              if (++spins > kSpinBusy) __builtin_amdgcn_s_sleep(2);
+              if (spins > kSpinLimit) {
                 dead = true;
                 if (lane == 0) atomicOr(&words->err, 1u);
               }
@@ -576,15 +580,35 @@ hipError_t prod(const double* A, int64_t lda, const double* B, int64_t ldb, doub
 // candidate to wait for, because a step's update and LDS traffic grow with
 // the rows per thread; two beyond that, to bound the candidates to read.
 //
-// Several workgroups wait for each other, so all of them have to run at once.  Up to
-// kPlainGroups of one row per thread they are launched like any other kernel: every
-// kernel beside them ends by itself, and those that wait in the same way (one for
-// each hardware queue of each process on the card, 16 processes of 4) need no more
-// than the two places that each of the 256 compute units has for such workgroups (116
-// registers, 8 waves); a wait that lasts all the same ends at kSpinLimit with the error
-// word set.  A cooperative launch idles about 11 us before and after it (n = 4096, 96
-// panels of 82 us: 15.7 ms with it, 13.8 without) and remains for more workgroups.
-constexpr int64_t kPlainGroups = kWaves;
+// Several workgroups wait for each other, so all of them have to run at once.  Few of
+// one row per thread are launched like any other kernel where the device has room
+// for many such panels (plain_groups): every kernel beside them ends by itself, and a
+// wait that lasts all the same ends at kSpinLimit with the error word set.  A
+// cooperative launch idles about 11 us before and after it (n = 4096, 96 panels of 82
+// us: 15.7 ms with it, 13.8 without) and remains for more workgroups and for smaller
+// devices.
+
+// Panels' workgroups of one row per thread that the current device has room for;
+// looked up once per device.
+hipError_t panel_places(int* places) {
+  constexpr int kMaxDevices = 64;
+  static std::atomic<int> known[kMaxDevices];
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  int v = dev >= 0 && dev < kMaxDevices ? known[dev].load(std::memory_order_relaxed) : 0;
+  if (v == 0) {
+    int per = 0, units = 0;
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &per, reinterpret_cast<const void*>(piv_panel_kernel<1, true>), kThreads, 0);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    v = per * units;
+    if (dev >= 0 && dev < kMaxDevices) known[dev].store(v, std::memory_order_relaxed);
+  }
+  *places = v;
+  return hipSuccess;
+}
 
 template <int RPT, bool MULTI>
 hipError_t launch_panel(double* A, int64_t lda, int64_t c, int h, int w, int64_t* ipiv,
@@ -594,7 +618,12 @@ hipError_t launch_panel(double* A, int64_t lda, int64_t c, int h, int w, int64_t
     return hipGetLastError();
   } else {
     const int64_t groups = ceil_div(h, kThreads * RPT);
-    if (RPT == 1 && groups <= kPlainGroups) {
+    int places = 0;
+    if (RPT == 1) {
+      const hipError_t e = panel_places(&places);
+      if (e != hipSuccess) return e;
+    }
+    if (RPT == 1 && groups <= plain_groups(places)) {
       piv_panel_kernel<RPT, true><<<(unsigned)groups, kThreads, 0, s>>>(A, lda, c, c, h, w, ipiv,
                                                                        slots, words, mv);
       return hipGetLastError();

@@ -203,3 +203,27 @@ def test_row_swaps_any_order(torch, T, n, k, k0, k1):
         B[[i, ip[i]]] = B[[ip[i], i]]
     assert np.array_equal(buf[:, :k].cpu().numpy(), B)
     assert bool(torch.isnan(buf[:, k:]).all())
+
+
+def test_panels_of_two_streams_wait_beside_each_other(torch, T):
+    # panels of several workgroups on two streams at once: each factorization has
+    # the bits it has alone
+    As = [torch.from_numpy(gen.rng(60 + n).standard_normal((n, n))).cuda() for n in (2049, 4096)]
+    fs = [T.LUPiv(A.shape[0], device=A.device) for A in As]
+    alone = []
+    for A, f in zip(As, fs):
+        F = A.clone()
+        f.factor(F)
+        assert f.check() == (T.OK, -1)
+        alone.append((F, f.ipiv.clone(), f.linv_blocks().clone()))
+    Fs = [[A.clone() for _ in range(3)] for A in As]
+    torch.cuda.synchronize()
+    for A, f, F in zip(As, fs, Fs):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for x in F:
+                f.factor(x)
+    torch.cuda.synchronize()
+    for f, F, (F0, p0, V0) in zip(fs, Fs, alone):
+        assert f.check() == (T.OK, -1)
+        assert all(torch.equal(x, F0) for x in F)
+        assert torch.equal(f.ipiv, p0) and torch.equal(f.linv_blocks(), V0)

@@ -84,3 +84,21 @@ def test_moves_stay_inside_the_panel(tmp_path, disagree):
     # unwritten, which is what the rule is for
     assert lost == 0
     assert (stale > 0) == disagree
+
+
+def test_waiting_panels_find_their_places(tmp_path):
+    # kPanelsAtOnce ordinary panels and the largest cooperative one (two rows per
+    # thread: the room of two) fit the device at once, whatever its size; the
+    # largest device keeps panels of 4096 rows out of the cooperative launch
+    out = run_program(tmp_path, r"""
+int main() {
+  for (int places = 0; places <= 4096; ++places) {
+    const int g = plain_groups(places);
+    if (g < 0 || g > kMaxPlainGroups) return 1;
+    if (g > 0 && kPanelsAtOnce * g + 2 * kMaxGroups > places) return 2;
+  }
+  printf("%d %d %d %d\n", plain_groups(512) * kPanelThreads, plain_groups(256) * kPanelThreads,
+         plain_groups(64), plain_groups(0));
+}
+""")
+    assert out.split() == ["4096", "2048", "0", "0"]
