@@ -36,7 +36,6 @@ inline unsigned grid_for(int64_t work, int threads, int64_t cap = 1 << 20) {
 // All of n = 16384 in squares of 128: 21 us.
 // ---------------------------------------------------------------------------
 constexpr int kInvNt = kInvRows / 16;
-constexpr int kInvThreads = 1024;       // a wave for each tile of the largest combine
 
 // TS: the square's rows, or 0 for `small` of them (below kInvRows).
 template <typename TL, int TS>
@@ -64,9 +63,9 @@ __global__ __launch_bounds__(kInvThreads) void block_inverse_kernel(
   if (bad && id == 0 && tid == 0) *bad = ~0ull;
   const int64_t gr0 = b * n0 + (int64_t)ti * ts, gc0 = b * n0 + (int64_t)tj * ts;
   double* __restrict__ out = Linv + b * n0 * n0 + (int64_t)ti * ts * n0 + (int64_t)tj * ts;
-  const int lg = 31 - __builtin_clz(ts);
   // A thread's elements: `fast` along L's rows in memory, `slow` = s0 + q ds.
-  const int fast = tid & (ts - 1), s0 = tid >> lg, ds = kInvThreads >> lg;
+  const SquareShare own = square_share(tid, ts);
+  const int fast = own.fast, s0 = own.s0, ds = own.ds;
   constexpr int kEach = kInvRows * kInvRows / kInvThreads;
   const int64_t slow0 = upper ? gc0 : gr0, fast0 = upper ? gr0 : gc0;
   const int slows = (int)min((int64_t)ts, n - slow0), fasts = (int)min((int64_t)ts, n - fast0);
@@ -150,8 +149,10 @@ __global__ __launch_bounds__(kInvThreads) void block_inverse_kernel(
   double* __restrict__ o = out + ((int64_t)s0 * n0 + fast);
 #pragma unroll
   for (int q = 0; q < kEach; ++q) {
-    const int i = s0 + q * ds;
-    const double x = Map::at(S, tile_of(q), min(ft, tile_of(q)))[in_tile(q) * kTld + fr];
+    if (!TS && q >= own.most) break;
+    const int i = s0 + q * ds, r = TS ? i : square_line(own, q, ts);
+    const int rt = TS ? tile_of(q) : r >> 4;
+    const double x = Map::at(S, rt, min(ft, rt))[(TS ? in_tile(q) : r & 15) * kTld + fr];
     if (i < ts) o[q * (ds * n0)] = fast <= i ? x : 0.0;
   }
 }

@@ -2,11 +2,9 @@
 #pragma once
 
 #include "common.hpp"
+#include "square.hpp"
 
 namespace trsm {
-
-// Rows of the squares inverted in LDS.
-constexpr int kInvRows = 128;
 
 // The m diagonal n0 x n0 blocks of L (lower part) in the packed binary64 buffer
 // Linv with every diagonal square of min(n0, kInvRows) rows inverted (zeros
