@@ -204,8 +204,8 @@ __device__ __forceinline__ void tile_store(double* c, const d4& v, double s = 1.
 // diagonal is one, whatever is stored there, and stays as it is; the other
 // triangle is not touched).  Alg. RecTriInv inside the tile: the four 4 x 4
 // diagonal blocks by substitution, one column a lane, then the combine for 4 and
-// 8 rows, as products of the whole tile with the blocks that take no part masked
-// to zero.
+// 8 rows (in the order of `combine`), as products of the whole tile with the blocks
+// that take no part masked to zero.
 __device__ __forceinline__ void invert_tile(double* x, bool upper, bool unit) {
   const int lane = fresh_lane(), gi = lane & 15, g = lane >> 4;
   if (lane < 16) {
@@ -238,7 +238,7 @@ __device__ __forceinline__ void invert_tile(double* x, bool upper, bool unit) {
       return (i & -(2 * h)) == (j & -(2 * h)) && (upper ? (j & h) > (i & h) : (i & h) > (j & h));
     };
 #pragma unroll 1
-    for (int step = 0; step < 2; ++step) {   // the inverse from the left, then from the right
+    for (int step = 0; step < 2; ++step) {   // the inverse from the right, then from the left
       double va[4], vb[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -246,8 +246,8 @@ __device__ __forceinline__ void invert_tile(double* x, bool upper, bool unit) {
         const double a = x[gi * kTld + k], b = x[k * kTld + gi];
         const double ai = inv(gi, k, a), ao = off(gi, k) ? -a : 0.0;
         const double bi = inv(k, gi, b), bo = off(k, gi) ? b : 0.0;
-        va[q] = step ? ao : ai;
-        vb[q] = step ? bi : bo;
+        va[q] = step ? ai : ao;
+        vb[q] = step ? bo : bi;
       }
       d4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -262,9 +262,13 @@ __device__ __forceinline__ void invert_tile(double* x, bool upper, bool unit) {
 // Alg. RecTriInv's combine for all pairs of blocks along the diagonal of an NT-tile
 // block (nt of them in use) whose diagonal tiles are already inverted, for Q =
 // 1, 2, ... tiles:
-//   lower: A21 := -(A22^{-1} A21) A11^{-1},  upper: A12 := -(A11^{-1} A12) A22^{-1},
+//   lower: A21 := -A22^{-1} A21 A11^{-1},  upper: A12 := -A11^{-1} A12 A22^{-1},
 // both products through registers, so no scratch is needed and the other
-// triangle is not touched.  unit as above.  One wave a tile: (NT / 2)^2 waves.
+// triangle is not touched.  Within 64 rows the product with the inverse on the right
+// comes first: its terms are those of a substitution, so that columns of any
+// scale stay in range (the other order overflows once two columns differ by more than
+// about 2^1023); above, the left one, as in the levels of larger blocks.
+// unit as above.  One wave a tile: (NT / 2)^2 waves.
 // One copy of the code serves all levels: a workgroup runs it once, so the time
 // to fetch an instruction counts as much as the time to run it.
 template <typename Map, int NT>
@@ -276,26 +280,27 @@ __device__ __forceinline__ void combine(double* S, int nt, bool upper, bool unit
     const int Q = 1 << lq, o = 2 * Q * (wave >> (2 * lq));
     const int hi = (wave >> lq) & (Q - 1), lo = wave & (Q - 1);
 #pragma unroll 1
-    for (int step = 0; step < 2; ++step) {   // the inverse from the left, then from the right
+    for (int step = 0; step < 2; ++step) {
+      const bool right = (step == 0) == (lq < 2);   // the inverse from the right
       // the coordinate that sets the cost varies over the waves of a SIMD
-      const int i = step ? lo : hi, j = step ? hi : lo;
+      const int i = right ? lo : hi, j = right ? hi : lo;
       auto tile = [&](int r, int c) {
         return upper ? Map::at(S, o + r, o + Q + c) : Map::at(S, o + Q + r, o + c);
       };
       const bool in = wave < NT * Q / 2 && o + Q + (upper ? j : i) < nt;
       d4 acc = {0.0, 0.0, 0.0, 0.0};
       if (in) {
-        const int f = (step == 0) != upper ? o + Q : o;   // the diagonal block that multiplies
+        const int f = right == upper ? o + Q : o;   // the diagonal block that multiplies
         // its tiles (d, k) or (k, d), and the diagonal one of them, k = d
-        const int d = step ? j : i;
-        const bool up = upper != (step == 1);             // k runs from d up, or from 0 to d
+        const int d = right ? j : i;
+        const bool up = upper != right;             // k runs from d up, or from 0 to d
         const int k0 = up ? d : 0;
         int k1 = up ? Q : d + 1;
-        if (upper == false && step == 0) k1 = min(k1, nt - o - Q);
+        if (!upper && !right) k1 = min(k1, nt - o - Q);
 #pragma unroll 1
         for (int k = k0; k < k1; ++k) {
-          const double* a = step ? tile(i, k) : Map::at(S, f + d, f + k);
-          const double* b = step ? Map::at(S, f + k, f + d) : tile(k, j);
+          const double* a = right ? tile(i, k) : Map::at(S, f + d, f + k);
+          const double* b = right ? Map::at(S, f + k, f + d) : tile(k, j);
           double va[4], vb[4];
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
@@ -305,8 +310,8 @@ __device__ __forceinline__ void combine(double* S, int nt, bool upper, bool unit
           if (k == d) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-              const int r = step ? 4 * q + g : gi, c = step ? gi : 4 * q + g;
-              double& v = step ? vb[q] : va[q];
+              const int r = right ? 4 * q + g : gi, c = right ? gi : 4 * q + g;
+              double& v = right ? vb[q] : va[q];
               v = unit && r == c ? 1.0 : (upper ? c >= r : c <= r) ? v : 0.0;
             }
           }

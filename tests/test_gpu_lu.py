@@ -117,6 +117,23 @@ def test_leaf_tiles(torch, T, n, scale):
         assert f.check() == (T.ESINGULAR, bad)
 
 
+@pytest.mark.parametrize("split", [4, 8, 16, 32])
+def test_columns_of_very_different_scale(torch, T, split):
+    # A = A0 E with powers of two on E's diagonal that differ by 2^1200: L and its
+    # inverse are A0's, U = U0 E and its inverse E^-1 U0^-1, all to the last bit (every
+    # operation scales exactly, and every term of a substitution is in range)
+    n = 64
+    A = gen.diag_dominant(n, 31)
+    e = np.where(np.arange(n) // split % 2 == 0, 2.0 ** -600, 2.0 ** 600)
+    L0, U0, _, f0 = gpu_lu(torch, T, A)
+    L, U, _, f = gpu_lu(torch, T, A * e)
+    assert f.check() == (T.OK, -1)
+    assert np.array_equal(L, L0) and np.array_equal(U, U0 * e)
+    assert torch.equal(f.linv_blocks(), f0.linv_blocks())
+    V0, V = f0.uinv_blocks().cpu().numpy()[0], f.uinv_blocks().cpu().numpy()[0]
+    assert np.array_equal(V * e[:, None], V0)
+
+
 @pytest.mark.parametrize("pad", [0, 1])
 @pytest.mark.parametrize("n,nb", [(65, 128), (66, 128), (79, 128), (81, 128), (127, 128),
                                   (129, 256), (193, 256), (255, 256), (257, 128), (260, 128)])

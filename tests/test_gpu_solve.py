@@ -162,6 +162,22 @@ def test_integer_system_is_exact(torch, T):
         assert np.array_equal(X, Xtrue), n0
 
 
+@pytest.mark.parametrize("split", [4, 8, 16, 32])
+@pytest.mark.parametrize("n,n0", [(64, 64), (100, 64), (33, 32)])
+def test_columns_of_very_different_scale(torch, T, n, n0, split):
+    # L = L0 D with powers of two on D's diagonal that differ by 2^1200: every term
+    # of a substitution is in range, and every operation scales exactly, so X is
+    # D^-1 X0 to the last bit; likewise U = D U0 with B = D B0 and X = X0
+    L, B = gen.easy_system(n, 5, 21)
+    d = np.where(np.arange(n) // split % 2 == 0, 2.0 ** 600, 2.0 ** -600)
+    X0 = gpu_solve(torch, T, L, B, n0=n0)
+    assert np.array_equal(gpu_solve(torch, T, L * d, B, n0=n0) * d[:, None], X0)
+    U = np.ascontiguousarray(L.T)
+    X0 = gpu_solve(torch, T, U, B, n0=n0, flags=T.FLAG_UPPER)
+    X = gpu_solve(torch, T, U * d[:, None], B * d[:, None], n0=n0, flags=T.FLAG_UPPER)
+    assert np.array_equal(X, X0)
+
+
 @pytest.mark.parametrize("n0", [64, 256, 512])
 def test_block_inverses_match_oracle(torch, T, n0):
     n = 1000
