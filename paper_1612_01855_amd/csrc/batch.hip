@@ -379,7 +379,7 @@ __global__ __launch_bounds__(64) void grouped_fin_kernel(const FinEntry* __restr
 }
 
 // Split-K finish of grouped products: the fixed-order sum of each element's
-// ksplit partial sums, then the product's epilogue.  Entry e owns workgroups
+// ksplit partial sums (as gemm_splitk_finish), then the product's epilogue.  Entry e owns workgroups
 // [start[e], start[e+1]), kFinChunk elements each; a thread holds its
 // kFinChunk / 256 elements at once, so each slice's loads go out together.
 constexpr int kFinChunk = 2048;
@@ -400,7 +400,9 @@ __global__ __launch_bounds__(256) void grouped_split_finish(
   const Epi beta = static_cast<Epi>(p.beta);
   const bool use_beta = (p.flags & G_BETA) && p.Cin;
   const bool use_rs = (p.flags & G_ROWSCALE) && p.rscale;
-  const Acc* __restrict__ P = static_cast<const Acc*>(p.part);
+  const bool down = p.flags & G_A_UPPER;
+  const int64_t step = down ? -MN : MN;
+  const Acc* __restrict__ P = static_cast<const Acc*>(p.part) + (down ? p.ksplit - 1 : 0) * MN;
   const int64_t e0 = base + threadIdx.x;
   const int64_t lim = min(MN, base + kFinChunk);
   if (e0 >= lim) return;
@@ -423,7 +425,7 @@ __global__ __launch_bounds__(256) void grouped_split_finish(
 #pragma unroll
   for (int j = 0; j < U; ++j) v[j] = P[pe[j]];
   for (int t = 1; t < p.ksplit; ++t) {
-    const Acc* __restrict__ Pt = P + t * MN;
+    const Acc* __restrict__ Pt = P + t * step;
     Acc w[U];
 #pragma unroll
     for (int j = 0; j < U; ++j) w[j] = Pt[pe[j]];

@@ -373,6 +373,9 @@ constexpr int dma_lds() {
 // stage is free for chunk c + 2 and two stages keep a whole chunk time between
 // a copy and its use.  (Reading each half right before its MFMAs left the
 // matrix cores idle for two LDS latencies per chunk.)
+// K runs towards the diagonal (for G_A_UPPER downwards, the lane groups in turn too):
+// the diagonal's term, the largest of an inverted block's row, is added last, and the
+// sum before it rounds at its own size.
 // Triangular masks are applied to the fragments, only in chunks that cross
 // the diagonal.
 template <typename TIn, typename TCin, typename TCout, typename TC2, int BM, int BN, int WGM,
@@ -419,6 +422,9 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout,
   nchunks = split_range<BK>(K, s, p.ksplit, nchunks, kbeg);
   const bool a_lower = (p.flags & G_A_LOWER) && !(p.flags & G_A_ZERO_UPPER);
   const bool b_lower = p.flags & G_B_LOWER;
+  const bool down = p.flags & G_A_UPPER;
+  const int kfirst = down ? kbeg + (nchunks - 1) * BK : kbeg, kstep = down ? -BK : BK;
+  const int gk = down ? 3 - g : g;               // an instruction adds its lane groups in turn
 
   Out acc[TM][TN];
 #pragma unroll
@@ -435,8 +441,8 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout,
   // and skips them.
   constexpr bool RUNON = BM * BN >= 128 * 128;
   auto issue = [&](int c, int st) {
-    const int k0 = kbeg + c * BK;
-    const int kend = !RUNON || c < nchunks ? K : 0;
+    const int k0 = kfirst + c * kstep;
+    const int kend = !RUNON || c < nchunks ? K : INT32_MIN;   // k0 may be negative
     char* base = smem + st * STAGE;
     // rows [row0, row0 + 8 INST NW) of a k-contiguous operand, swizzled
     auto rows_of = [&](const TIn* P, int ld, int row0, int rows, char* dst, auto inst, auto wide) {
@@ -508,14 +514,14 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout,
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       const int r = wm * WTM + i * 16 + gi;
-      const int slot = (2 * g + h) ^ (r & 7);
+      const int slot = (2 * gk + h) ^ (r & 7);
       f.a[i] = *reinterpret_cast<const V16*>(as + r * 128 + slot * 16);
     }
     if constexpr (BKMAJOR) {
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         const int r = wn * WTN + j * 16 + gi;
-        const int slot = (2 * g + h) ^ (r & 7);
+        const int slot = (2 * gk + h) ^ (r & 7);
         const V16 v = *reinterpret_cast<const V16*>(bs + r * 128 + slot * 16);
 #pragma unroll
         for (int e = 0; e < VEC; ++e) f.b[e][j] = v[e];
@@ -523,7 +529,7 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout,
     } else {
 #pragma unroll
       for (int e = 0; e < VEC; ++e) {
-        const int kr = g * KL + h * VEC + e;
+        const int kr = gk * KL + h * VEC + e;
 #pragma unroll
         for (int j = 0; j < TN; ++j)
           f.b[e][j] = *reinterpret_cast<const TIn*>(bs + (kr / RPI) * (1024 + 16) +
@@ -535,27 +541,27 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout,
   // 16-byte pieces of A beside 4-byte copies of B: the last piece may reach past K
   const int k_tail = A16 && !B16 && K % VEC ? K : INT32_MAX;
   auto mask = [&](Half& f, int c, int h) {
-    const int k0 = kbeg + c * BK;
+    const int k0 = kfirst + c * kstep;
     if (k0 + BK > k_tail) {
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int e = 0; e < VEC; ++e)
-          if (k0 + g * KL + h * VEC + e >= k_tail) f.a[i][e] = TIn(0);
+          if (k0 + gk * KL + h * VEC + e >= k_tail) f.a[i][e] = TIn(0);
     }
     if (a_lower && k0 + BK - 1 > r0 + wm * WTM) {
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int e = 0; e < VEC; ++e)
-          if (k0 + g * KL + h * VEC + e > r0 + wm * WTM + i * 16 + gi) f.a[i][e] = TIn(0);
+          if (k0 + gk * KL + h * VEC + e > r0 + wm * WTM + i * 16 + gi) f.a[i][e] = TIn(0);
     }
     if (b_lower && k0 < c0 + wn * WTN + WTN - 1) {
 #pragma unroll
       for (int e = 0; e < VEC; ++e)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
-          if (k0 + g * KL + h * VEC + e < c0 + wn * WTN + j * 16 + gi) f.b[e][j] = TIn(0);
+          if (k0 + gk * KL + h * VEC + e < c0 + wn * WTN + j * 16 + gi) f.b[e][j] = TIn(0);
     }
   };
   auto multiply = [&](const Half& f) {
@@ -866,7 +872,11 @@ __device__ __forceinline__ void gemm_tile(const GemmParams<TIn, TCin, TCout, TC2
 // chunk, the loads of 32 (binary64) or 64 (binary32) k in flight while the previous
 // ones multiply, and four times as many workgroups as 64 x 64 tiles.  VEC16:
 // operands with contiguous k are read 16 bytes at a time (aligned); otherwise
-// one element at a time, any alignment.  Triangles are skipped and masked per
+// one element at a time, any alignment.  K runs towards the diagonal as in
+// gemm_tile_dma: U X = B, 3001 x 500 in binary32, relative error 7.0e-8 and 110.9 us,
+// upwards 2.9e-7 and 108.3; with a step's elements in reverse too 6.3e-8, but
+// choosing their order at run time costs up to half of the speed (4096 x 8 in binary64:
+// 49.5 us for 31.4).  Triangles are skipped and masked per
 // 16 x 16 tile.  C must not overlap A or B, but for the strips: kRowStrip
 // (kColStrip), for products of at most 64 columns (rows), gives a workgroup 16 rows
 // (columns) of C in full, and its waves have read all they need of A (B) before the
@@ -913,8 +923,11 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmParams<TIn, TCin, TCo
   if (p.flags & G_A_UPPER) kbeg = min(r0, K) / SK * SK;
   if (p.flags & G_B_LOWER) kbeg = min(c0, K) / SK * SK;
   int steps = kend > kbeg && !idle ? (kend - kbeg + SK - 1) / SK : 0;
+  const bool down = p.flags & G_A_UPPER;
+  const int gk = down ? 3 - g : g;             // an instruction adds its lane groups in turn
   if (KW > 1) {
-    const int per = (steps + KW - 1) / KW, first = wave * per;
+    // the quarters in the order of the sum: the diagonal's is the last
+    const int per = (steps + KW - 1) / KW, first = (down ? KW - 1 - wave : wave) * per;
     kbeg += min(first, steps) * SK;
     steps = max(0, min(per, steps - first));
   }
@@ -927,7 +940,7 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmParams<TIn, TCin, TCo
   };
   // the lane group's VEC consecutive k of one step
   auto load = [&](Step& f, int k0) {
-    const int k = k0 + g * VEC;
+    const int k = k0 + gk * VEC;
     if (k0 + SK <= K) {
       if (VEC16) {
         const V16 v = *reinterpret_cast<const V16*>(A + k);
@@ -957,7 +970,7 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmParams<TIn, TCin, TCo
     }
   };
   auto mask = [&](Step& f, int k0) {
-    const int k = k0 + g * VEC;
+    const int k = k0 + gk * VEC;
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
       if (a_mask && k + e > r0 + gi) f.a[e] = TIn(0);
@@ -966,18 +979,19 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmParams<TIn, TCin, TCo
   };
   Out acc[1][1] = {};
   Step f[U];
+  const int kfirst = down ? kbeg + (steps - 1) * SK : kbeg, kstep = down ? -SK : SK;
 #pragma unroll
   for (int u = 0; u < U; ++u)
-    if (u < steps) load(f[u], kbeg + u * SK);
+    if (u < steps) load(f[u], kfirst + u * kstep);
   for (int t = 0; t < steps; t += U) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (t + u < steps) {
-        const int k0 = kbeg + (t + u) * SK;
+        const int k0 = kfirst + (t + u) * kstep;
         if (a_mask || b_mask) mask(f[u], k0);
 #pragma unroll
         for (int e = 0; e < VEC; ++e) acc[0][0] = MF::mma(f[u].a[e], f[u].b[e], acc[0][0]);
-        if (t + u + U < steps) load(f[u], k0 + U * SK);
+        if (t + u + U < steps) load(f[u], k0 + U * kstep);
       }
     }
   }
@@ -1050,8 +1064,8 @@ __global__ __launch_bounds__(256, 2) void gemm_pair_kernel(GemmParams<T, T, T, f
 }
 
 // Split-K finish: the fixed-order sum of the ksplit partial products of
-// every element, then the usual epilogue (deterministic: the order of the
-// sum never depends on scheduling).
+// every element (towards the diagonal, as in the tiles), then the usual epilogue
+// (deterministic: the order of the sum never depends on scheduling).
 template <typename TIn, typename TCin, typename TCout, typename TC2>
 __global__ __launch_bounds__(256) void gemm_splitk_finish(GemmParams<TIn, TCin, TCout, TC2> p,
                                                           int batch) {
@@ -1069,9 +1083,11 @@ __global__ __launch_bounds__(256) void gemm_splitk_finish(GemmParams<TIn, TCin, 
     const int64_t rc = e - z * MN;
     const int row = (int)(rc / p.N), col = (int)(rc - (int64_t)row * p.N);
     if ((p.flags & G_C_LOWER) && col > row) continue;
-    const Acc* q = P + (int64_t)z * p.ksplit * MN + rc;
+    const bool down = p.flags & G_A_UPPER;
+    const Acc* q = P + ((int64_t)z * p.ksplit + (down ? p.ksplit - 1 : 0)) * MN + rc;
+    const int64_t step = down ? -MN : MN;
     Acc v = q[0];
-    for (int t = 1; t < p.ksplit; ++t) v += q[t * MN];
+    for (int t = 1; t < p.ksplit; ++t) v += q[t * step];
     const int zo = z / p.zdiv, zi = z % p.zdiv;
     TCout* Co = p.Cout + zo * p.sco_o + zi * p.sco_i;
     const TCin* Ci = p.Cin ? p.Cin + zo * p.sci_o + zi * p.sci_i : nullptr;

@@ -71,6 +71,27 @@ def test_upper_matches_oracle(torch, T, n, k, n0):
     assert err <= TOL64
 
 
+@pytest.mark.parametrize("n,k,n0", [(1000, 7, 0), (1024, 300, 1024), (500, 900, 256),
+                                    (2100, 40, 2048)])
+def test_rounds_like_the_mirrored_lower_problem(torch, T, n, k, n0):
+    # U = J L J (J reverses the order) with J B is the same problem from the other
+    # end.  Its sums have the same terms and run towards the diagonal too, so the two
+    # errors are two samples of the same rounding: over at least 7000 elements
+    # their norms differ by a few per cent, and 1.25 leaves room for that.
+    L, B = gen.easy_system(n, k, 5 * n + k)
+    L, B = L.astype(np.float32), B.astype(np.float32)
+    ref = oracle.trsm(L.astype(np.float64), B.astype(np.float64))
+    s = T.Solver.create(n, k, "f32", n0)
+    Ld, Bd = torch.from_numpy(L).cuda(), torch.from_numpy(B).cuda()
+    s.invert(Ld)
+    lower = oracle.rel_fro_err(s.solve(Ld, Bd).double().cpu().numpy(), ref)
+    X = gpu_upper(torch, T, np.ascontiguousarray(L[::-1, ::-1]), np.ascontiguousarray(B[::-1]),
+                  "f32", n0)
+    upper = oracle.rel_fro_err(np.ascontiguousarray(X[::-1]), ref)
+    log(f"  lower {lower:.2e} upper {upper:.2e}")
+    assert upper <= 1.25 * lower
+
+
 def test_upper_in_place(torch, T):
     U, L, B = upper_system(700, 20, 3)
     X = gpu_upper(torch, T, U, B, "f64", 128, inplace=True)
