@@ -461,50 +461,69 @@ __global__ __launch_bounds__(kMoveCols) void panel_apply_kernel(double* __restri
 // slot kPw + i: row ipiv[k + i] if it is outside the group and no earlier
 // exchange of the group names it), the group's exchanges are done on the slot
 // contents, and then every named row is loaded once and stored where its
-// contents belong, all loads before the first store.  One memory round trip
-// per group instead of one per exchange: 1000 exchanges on 10 columns take
-// 0.26 ms.
+// contents belong, all loads before the first store.  With few columns it is bound by
+// the instructions of one wave, so the rows' addresses are made by the lanes, one each,
+// and passed by readlane, and the next group's ipiv is on its way meanwhile.
+// Measured (one exchange at a time, a memory round trip each, in brackets): 4096
+// exchanges of 1 column 663 us (668), 1000 of 10 162 (165), 100 of 100000 44 (41), 8192 of
+// 8192 1990 (3610).
 constexpr int kSwapCols = 256;
 __global__ __launch_bounds__(kSwapCols) void swap_rows_kernel(double* __restrict__ B, int64_t ldb,
                                                               const int64_t* __restrict__ ipiv,
                                                               int64_t k0, int64_t k1,
                                                               int64_t ncols) {
-  const int64_t col = (int64_t)blockIdx.x * kSwapCols + threadIdx.x;
-  const bool live = col < ncols;
+  // All lanes of a wave stay active to the end: a value passed by readlane is lost
+  // where its lane is not.  Lanes past the last column repeat it (the same values to
+  // the same places), and a wave with none leaves.
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t first = (int64_t)blockIdx.x * kSwapCols + 64 * wave;   // the wave's first column
+  if (first >= ncols) return;
   const int lane = threadIdx.x & 63;
-  double* __restrict__ P = B + (live ? col : 0);
+  const unsigned c = (unsigned)min((int64_t)lane, ncols - 1 - first);
+  double* __restrict__ P = B + first;
+  // row `row` (relative to k) of these columns as a lane's address, and a lane's
+  // address for every lane
+  typedef __attribute__((address_space(1))) double* Row;
+  auto address = [&](int64_t k, int row) {
+    return __builtin_bit_cast(double, (Row)(P + (k + row) * ldb));
+  };
+  auto row_of = [&](double adr, int slot) {
+    return __builtin_bit_cast(Row, lane_value(adr, slot));
+  };
+  int64_t next = k0 + lane < k1 ? ipiv[k0 + lane] : k0;
   for (int64_t k = k0; k < k1; k += kPw) {
     const int w = (int)(k1 - k < kPw ? k1 - k : kPw);
-    // target of exchange `lane` (lanes 0 .. w-1), then slot contents: the
-    // group's row numbers relative to k, targets as 32-bit offsets
-    const int64_t q = lane < w ? ipiv[k + lane] : k;
+    // target of exchange `lane` (lanes 0 .. w-1) as a row relative to k
+    const int64_t q = lane < w ? next : k;
+    next = k + kPw + lane < k1 ? ipiv[k + kPw + lane] : k0;
     const int off = (int)(q - k);
-    int owner = kPw + lane;                 // the slot of this exchange's target
-    if (off >= 0 && off < w) owner = off;
+    const int far = __shfl(off, lane - kPw, 64);
+    const int place = lane < kPw ? lane : far;   // the row that this slot names
+    int cur = place;                             // and the row now in it
+    unsigned long long used = ~0ull >> (64 - w);
     for (int i = 0; i < w; ++i) {
       const int oi = __builtin_amdgcn_readlane(off, i);
-      if (lane > i && lane < w && oi == off && owner == kPw + lane) owner = kPw + i;
-    }
-    const int far = __shfl(off, lane - kPw, 64);
-    const int fown = __shfl(owner, lane - kPw, 64);
-    const bool used = lane < w || (lane >= kPw && lane - kPw < w && fown == lane);
-    const int place = lane < kPw ? lane : far;
-    int cur = place;                        // the row (relative to k) now in this slot
-    for (int i = 0; i < w; ++i) {
-      const int t = __builtin_amdgcn_readlane(owner, i);
+      // the slot of the target: its own in the group, or that of the first exchange with it
+      const unsigned long long same = __ballot(off == oi) & ~(~0ull << i);
+      const int t = oi >= 0 && oi < w ? oi : kPw + (same ? __ffsll(same) - 1 : i);
+      used |= 1ull << t;
       const int x = __builtin_amdgcn_readlane(cur, i), y = __builtin_amdgcn_readlane(cur, t);
       cur = lane == i ? y : (lane == t ? x : cur);
     }
-    const int from = used ? cur : 0, to = used ? place : 0;
+    const bool named = used >> lane & 1;
+    const double from = address(k, named ? cur : 0), to = address(k, named ? place : 0);
     double v[2 * kPw];
 #pragma unroll
-    for (int s = 0; s < 2 * kPw; ++s)
-      v[s] = P[(k + __builtin_amdgcn_readlane(from, s)) * ldb];
-    const bool moved = used && cur != place;
-    const unsigned long long mm = __ballot(moved);
+    for (int s = 0; s < 2 * kPw; ++s) {
+      v[s] = row_of(from, s)[c];
+      // (few addresses at a time: the scalar registers do not hold all of them)
+      if (s % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+    }
+    const unsigned long long mm = __ballot(named && cur != place);
+    asm volatile("" : "+v"(next));          // waited for here, not after the stores
 #pragma unroll
     for (int s = 0; s < 2 * kPw; ++s)
-      if (((mm >> s) & 1) && live) P[(k + __builtin_amdgcn_readlane(to, s)) * ldb] = v[s];
+      if ((mm >> s) & 1) row_of(to, s)[c] = v[s];
   }
 }
 

@@ -205,6 +205,23 @@ def test_row_swaps_any_order(torch, T, n, k, k0, k1):
     assert bool(torch.isnan(buf[:, k:]).all())
 
 
+@pytest.mark.parametrize("k", [2, 63, 64, 65, 200, 255, 256, 257, 321])
+def test_row_swaps_partial_waves(torch, T, k):
+    # the last wave with 1, most and all of its columns: its other lanes hold rows
+    # of the exchanges too
+    n = 130
+    g = gen.rng(k)
+    ip = np.arange(n) + (g.random(n) * (n - np.arange(n))).astype(np.int64)
+    B = g.standard_normal((n, k))
+    buf = torch.full((n, k + 1), float("nan"), dtype=torch.float64, device="cuda")
+    buf[:, :k] = torch.from_numpy(B).cuda()
+    ipd = torch.from_numpy(ip).cuda()
+    T.trsm_row_swaps(0, n, ipd.data_ptr(), buf.data_ptr(), k + 1, k,
+                     torch.cuda.current_stream().cuda_stream)
+    assert np.array_equal(buf[:, :k].cpu().numpy(), B[oracle.perm_from_ipiv(ip)])
+    assert bool(torch.isnan(buf[:, k:]).all())
+
+
 def test_panels_of_two_streams_wait_beside_each_other(torch, T):
     # panels of several workgroups on two streams at once: each factorization has
     # the bits it has alone
