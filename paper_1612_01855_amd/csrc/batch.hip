@@ -483,7 +483,7 @@ constexpr int kPassBlocks = 4;
 template <typename T, bool ALIGNED>
 __device__ __forceinline__ void persist_tile(const GemmParams<T, T, T, float>& p, char* smem) {
   if constexpr (ALIGNED)
-    gemm_tile_dma<T, T, T, float, kPB, kPB, 2, 2>(p, 0, 0, 0, 0, smem);
+    gemm_tile_dma<T, T, T, float, kPB, kPB, 2, 2, false, true, true, false>(p, 0, 0, 0, 0, smem);
   else
     gemm_tile_staged<T, T, T, float, kPB, kPB, 2, 2, false, false>(p, 0, 0, 0, 0);
 }
