@@ -1245,20 +1245,39 @@ inline hipError_t launch_direct(const GemmParams<TIn, TCin, TCout, TC2>& p, int 
 // it, so the tiles take as long as the fullest of 256 units; the finish pass
 // of a split takes 4 us and reads and writes S + 2 times C at 3 TB/s.  Measured at
 // N = 128, K = 1024, binary64: 480 workgroups (M = 15360) 89 us unsplit and 95 in
-// two, 256 (8192) 49 and 54, 64 (2048) 45 and, in eight, 25.
+// two, 256 (8192) 49 and 54, 64 (2048) 45 and, in eight, 25.  With one column tile no
+// neighbour brings A's rows into the cache: a chunk then takes 1.0 us alone on its unit,
+// 0.6 each beside others.
+//
+// Folded triangles: a workgroup's two tiles have nck + 4 chunks together, but a slice of
+// K cuts both of them in the lower half and one in the upper, so the longest slice
+// has twice the mean.  It sets the time of few slices (0.7 us a chunk); many
+// slices run at 0.6 us a chunk and unit and leave a quarter of the longest over.
+// n = 8192 by 8 columns, binary64 (S = 1, 4, 8, 16): 360, 185, 121, 99 us; 4096 by 300:
+// 170, 155, 128, 130; 2048 by 400: 90, 66, 59, 65.
 template <typename TIn, typename P>
 inline int chain_ksplit(const P& p, int64_t wgs, int batch) {
   if (!p.part) return 1;
   constexpr int BK = 128 / sizeof(TIn);
   const int64_t nck = (p.K + BK - 1) / BK;
   const int64_t per = (int64_t)p.M * p.N * batch * (int64_t)sizeof(typename Mfma<TIn>::Acc);
-  const double chunk = sizeof(TIn) == 8 ? 0.70 : 0.9;
+  const bool fold = tri_fold(p.M, p.K, p.flags, 64);
+  const double alone = p.N <= 64 ? 1.0 : sizeof(TIn) == 8 ? 0.70 : 0.9;
+  const double each = p.N <= 64 ? 0.6 : alone;
   int best = 1;
   double least = 1e300;
   for (int64_t S = 1; S <= kSplitMax; ++S) {
     if (S > 1 && (nck / S < kSplitMinChunks || S * per > p.part_bytes)) break;
-    const double t = (double)((wgs * S + 255) / 256) * (double)((nck + S - 1) / S) * chunk +
-                     (S > 1 ? 4.0 + (double)(S + 2) * (double)per / 3e6 : 0.0);
+    const double cps = (double)((nck + S - 1) / S);
+    double t;
+    if (fold) {
+      const double longest = 0.7 * (S > 1 ? std::min(2 * cps, (double)nck + 4) : (double)nck + 4);
+      t = std::max(longest, 0.6 * (double)(wgs * (nck + 4)) / 256 + longest / 4);
+    } else {
+      const int64_t on_unit = (wgs * S + 255) / 256;
+      t = cps * std::max(alone, (double)on_unit * each);
+    }
+    if (S > 1) t += 4.0 + (double)(S + 2) * (double)per / (fold ? 8e6 : 3e6);
     if (t < least) {
       least = t;
       best = (int)S;
