@@ -44,6 +44,8 @@ namespace trsm {
 
 // How a product's operands reach LDS (gemm_mode).
 enum GemmMode { kStaged, kDma4, kDma16A, kDma16 };
+// Which way a tile runs through K: as its flags say, or known when compiled.
+enum GemmDir { kByFlags, kUp, kDown };
 
 enum GemmFlags : uint32_t {
   G_A_LOWER = 1u,
@@ -383,7 +385,8 @@ constexpr int dma_lds() {
 // Triangular masks are applied to the fragments, only in chunks that cross
 // the diagonal.
 template <typename TIn, typename TCin, typename TCout, typename TC2, int BM, int BN, int WGM,
-          int WGN, bool BKMAJOR = false, bool A16 = true, bool B16 = true, bool AHEAD = true>
+          int WGN, bool BKMAJOR = false, bool A16 = true, bool B16 = true, bool AHEAD = true,
+          int DIR = kByFlags>
 __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout, TC2>& p, int z,
                                               int s, const int r0, const int c0,
                                               char* const smem) {
@@ -426,7 +429,7 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout,
   nchunks = split_range<BK>(K, s, p.ksplit, nchunks, kbeg);
   const bool a_lower = (p.flags & G_A_LOWER) && !(p.flags & G_A_ZERO_UPPER);
   const bool b_lower = p.flags & G_B_LOWER;
-  const bool down = p.flags & G_A_UPPER;
+  const bool down = DIR == kByFlags ? p.flags & G_A_UPPER : DIR == kDown;
   const int kfirst = down ? kbeg + (nchunks - 1) * BK : kbeg, kstep = down ? -BK : BK;
   const int gk = down ? 3 - g : g;               // an instruction adds its lane groups in turn
 
@@ -446,7 +449,7 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout,
   constexpr bool RUNON = BM * BN >= 128 * 128;
   auto issue = [&](int c, int st) {
     const int k0 = kfirst + c * kstep;
-    const int kend = !RUNON || c < nchunks ? K : INT32_MIN;   // k0 may be negative
+    const int kend = !RUNON || c < nchunks ? K : DIR == kUp ? 0 : INT32_MIN;   // (k0 < 0 downwards)
     char* base = smem + st * STAGE;
     // rows [row0, row0 + 8 INST NW) of a k-contiguous operand, swizzled
     auto rows_of = [&](const TIn* P, int ld, int row0, int rows, char* dst, auto inst, auto wide) {
@@ -577,8 +580,8 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout,
         for (int j = 0; j < TN; ++j) acc[i][j] = MF::mma(f.a[i][e], f.b[e][j], acc[i][j]);
   };
 
-  const bool masked = a_lower || b_lower || k_tail != INT32_MAX;
   if constexpr (!AHEAD) {
+    const bool masked = a_lower || b_lower || k_tail != INT32_MAX;
     if (nchunks > 0) issue(0, 0);
     for (int c = 0; c < nchunks; ++c) {
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // this wave's part of chunk c has landed
@@ -606,6 +609,7 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmParams<TIn, TCin, TCout,
     }
     __syncthreads();                                // ... everyone's
     fetch(f0, 0, 0);
+    const bool masked = a_lower || b_lower || k_tail != INT32_MAX;
     for (int c = 0; c < nchunks; ++c) {
       // the reads go out before the MFMAs (the scheduler would sink them)
       fetch(f1, c, 1);
@@ -852,14 +856,14 @@ constexpr int tile_lds() {
 
 template <typename TIn, typename TCin, typename TCout, typename TC2,
           int BM, int BN, int WGM, int WGN, bool BKMAJOR, int MODE, bool CLOWER = false,
-          int GROUP_M = 8, bool XCD_REMAP = false>
+          int DIR = kByFlags, int GROUP_M = 8, bool XCD_REMAP = false>
 __device__ __forceinline__ void gemm_tile(const GemmParams<TIn, TCin, TCout, TC2>& p, int z,
                                           int s, int bid, int nwg, char* smem) {
   const int ntm = (p.M + BM - 1) / BM, ntn = (p.N + BN - 1) / BN;
   auto one = [&](int tm, int tn) {
     if constexpr (MODE != kStaged && Mfma<TIn>::kPerLane == 1)
-      gemm_tile_dma<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, MODE != kDma4, MODE == kDma16>(
-          p, z, s, tm * BM, tn * BN, smem);
+      gemm_tile_dma<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, MODE != kDma4, MODE == kDma16,
+                    true, DIR>(p, z, s, tm * BM, tn * BN, smem);
     else
       gemm_tile_staged<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, MODE == kDma16>(
           p, z, s, tm * BM, tn * BN);
@@ -1057,11 +1061,12 @@ __global__ __launch_bounds__(256) void gemm_direct_pair_kernel(GemmParams<T, T, 
 }
 
 template <typename TIn, typename TCin, typename TCout, typename TC2,
-          int BM, int BN, int WGM, int WGN, bool BKMAJOR, int MODE, bool CLOWER = false>
+          int BM, int BN, int WGM, int WGN, bool BKMAJOR, int MODE, bool CLOWER = false,
+          int DIR = kByFlags>
 __global__ __launch_bounds__(WGM * WGN * 64, 2)
 void gemm_kernel(GemmParams<TIn, TCin, TCout, TC2> p) {
   __shared__ __attribute__((aligned(1024))) char smem[tile_lds<TIn, BM, BN, BKMAJOR, MODE>()];
-  gemm_tile<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, MODE, CLOWER>(
+  gemm_tile<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, MODE, CLOWER, DIR>(
       p, blockIdx.z, blockIdx.y, blockIdx.x, gridDim.x, smem);
 }
 
@@ -1332,9 +1337,16 @@ inline hipError_t launch_gemm(const GemmParams<TIn, TCin, TCout, TC2>& p, int ba
   dim3 grid((unsigned)tiles, (unsigned)q.ksplit, (unsigned)batch);
   dim3 block(WGM * WGN * 64);
   auto go = [&](auto kernel) { kernel<<<grid, block, 0, stream>>>(q); };
+  // one for each direction of K: chosen at run time it costs binary32 1 % (16384 x
+  // 16384 by 2048: 4850 and 4900 us)
+  constexpr int kDirUp = kDirect ? kUp : kByFlags, kDirDown = kDirect ? kDown : kByFlags;
   if (mode == kDma16) {
-    if (clower) go(gemm_kernel<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, kDma16, true>);
-    else go(gemm_kernel<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, kDma16>);
+    if (clower)
+      go(gemm_kernel<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, kDma16, true, kDirUp>);
+    else if (kDirect && (p.flags & G_A_UPPER))
+      go(gemm_kernel<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, kDma16, false, kDirDown>);
+    else
+      go(gemm_kernel<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, kDma16, false, kDirUp>);
   } else if (mode == kStaged) {
     if (clower) go(gemm_kernel<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, kStaged, true>);
     else go(gemm_kernel<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, kStaged>);
