@@ -92,7 +92,8 @@ typedef struct trsm_plan_info {
   int64_t n, k;            /* problem sizes the plan was made for */
   int64_t n0;              /* diagonal block size used (a power of two) */
   int64_t m;               /* number of diagonal blocks, ceil(n / n0) */
-  int64_t leaf;            /* size of the blocks inverted directly in LDS */
+  int64_t leaf;            /* min(n0, 64): rows up to which a block's inverse is made of a
+                              substitution's terms (LDS takes squares of up to 128 rows) */
   int64_t n0_paper_rule;   /* the Sec. VIII rule evaluated at p = 1 (reported, not used) */
   int32_t precision;       /* trsm_precision */
   uint32_t flags;

@@ -1225,12 +1225,11 @@ inline bool direct_vec(const P& p) {
 // over a workgroup's waves unless there are many tiles or hardly any steps.
 template <typename TIn, typename TCin, typename TCout, typename TC2, bool BKMAJOR>
 inline hipError_t launch_direct(const GemmParams<TIn, TCin, TCout, TC2>& p, int batch,
-                                hipStream_t stream, int kw = 0) {
+                                hipStream_t stream) {
   GemmParams<TIn, TCin, TCout, TC2> q = p;
   q.ksplit = 1;
   const unsigned ntm = (unsigned)((p.M + 15) / 16), ntn = (unsigned)((p.N + 15) / 16);
-  if (kw == 0)
-    kw = (int64_t)ntm * ntn * batch > 2048 || p.K * (int)sizeof(TIn) < 512 ? 1 : 4;
+  const int kw = (int64_t)ntm * ntn * batch > 2048 || p.K * (int)sizeof(TIn) < 512 ? 1 : 4;
   const dim3 grid(kw == 1 ? ((ntm + 1) / 2) * ((ntn + 1) / 2) : ntm * ntn, 1, (unsigned)batch);
   const bool vec = direct_vec<TIn, BKMAJOR>(p);
   auto go = [&](auto kernel) { kernel<<<grid, 256, 0, stream>>>(q); };

@@ -62,7 +62,6 @@ inline size_t al(size_t v) { return (v + kAl - 1) / kAl * kAl; }
 // Status words at the start of the workspace.
 struct Words {
   unsigned long long bad;   // smallest column with a zero or non-finite pivot
-  unsigned unused;
   unsigned err;             // a wait for a candidate gave up
 };
 
@@ -531,12 +530,6 @@ __global__ __launch_bounds__(kSwapCols) void swap_rows_kernel(double* __restrict
   do {                                                            \
     hipError_t e_ = (__VA_ARGS__);                                \
     if (e_ != hipSuccess) return (trsm_status)note_hip_error(e_); \
-  } while (0)
-
-#define PIV_TRY(...)                 \
-  do {                               \
-    trsm_status s_ = (__VA_ARGS__);  \
-    if (s_ != TRSM_OK) return s_;    \
   } while (0)
 
 struct Layout {
