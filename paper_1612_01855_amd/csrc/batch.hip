@@ -599,7 +599,7 @@ hipError_t launch_persist(const void* items, const void* tasks, int ntasks, unsi
 // launches a phase, 80 in one).
 constexpr int form_of(int shape, int mode) { return shape * (kDma16 + 1) + mode; }
 
-template <typename T>
+template <typename T, int DIR>
 __global__ __launch_bounds__(256, 2) void gemm_forms_kernel(
     const GemmParams<T, T, T, float>* __restrict__ entries, const int* __restrict__ start, int n) {
   constexpr int kNarrowLds = dma_lds<T, kBM, kNarrowN, false>();
@@ -610,13 +610,13 @@ __global__ __launch_bounds__(256, 2) void gemm_forms_kernel(
   const int local = (int)blockIdx.x - start[lo];
   auto narrow = [&](auto mode) {
     const int tiles = gemm_wgs(p.M, p.N, p.K, p.flags, kBM, kNarrowN);
-    gemm_tile<T, T, T, float, kBM, kNarrowN, 4, 1, false, mode()>(p, 0, local / tiles,
-                                                                 local % tiles, tiles, smem);
+    gemm_tile<T, T, T, float, kBM, kNarrowN, 4, 1, false, mode(), false, DIR>(
+        p, 0, local / tiles, local % tiles, tiles, smem);
   };
   auto mid = [&](auto mode) {
     const int tiles = gemm_wgs(p.M, p.N, p.K, p.flags, kMidTile, kMidTile);
-    gemm_tile<T, T, T, float, kMidTile, kMidTile, 2, 2, false, mode()>(p, 0, local / tiles,
-                                                                      local % tiles, tiles, smem);
+    gemm_tile<T, T, T, float, kMidTile, kMidTile, 2, 2, false, mode(), false, DIR>(
+        p, 0, local / tiles, local % tiles, tiles, smem);
   };
   switch (__builtin_amdgcn_readfirstlane(start[n + 1 + lo])) {
     case form_of(kNarrow, kDma4): narrow(std::integral_constant<int, kDma4>()); break;
@@ -628,18 +628,26 @@ __global__ __launch_bounds__(256, 2) void gemm_forms_kernel(
   }
 }
 
-// One grouped launch.
-template <typename T>
-void launch_grouped(const GemmParams<T, T, T, float>* e, const int* start, int count, int shape,
-                    int mode, dim3 grid, hipStream_t s) {
+// One grouped launch.  Without upper triangles the way through K is known when
+// compiled (48 uneven systems in binary32: 80.0 us, chosen at run time 80.9).
+template <typename T, int DIR>
+void launch_grouped_dir(const GemmParams<T, T, T, float>* e, const int* start, int count, int shape,
+                        int mode, dim3 grid, hipStream_t s) {
   if (shape != kWide)
-    gemm_forms_kernel<T><<<grid, 256, 0, s>>>(e, start, count);
+    gemm_forms_kernel<T, DIR><<<grid, 256, 0, s>>>(e, start, count);
   else if (mode == kDma16)
-    gemm_grouped_kernel<T, T, T, float, kBM, kBN, 2, 2, false, kDma16>
+    gemm_grouped_kernel<T, T, T, float, kBM, kBN, 2, 2, false, kDma16, DIR>
         <<<grid, 256, 0, s>>>(e, start, count);
   else
     gemm_grouped_kernel<T, T, T, float, kBM, kBN, 2, 2, false, kStaged>
         <<<grid, 256, 0, s>>>(e, start, count);
+}
+
+template <typename T>
+void launch_grouped(const GemmParams<T, T, T, float>* e, const int* start, int count, int shape,
+                    int mode, bool upper, dim3 grid, hipStream_t s) {
+  if (upper) launch_grouped_dir<T, kByFlags>(e, start, count, shape, mode, grid, s);
+  else launch_grouped_dir<T, kUp>(e, start, count, shape, mode, grid, s);
 }
 
 }  // namespace
@@ -728,6 +736,7 @@ void LaunchList::add_gemm(int kind, int split_kind, std::vector<P> entries) {
       st[i + 1] = st[i] + gemm_wgs(e.M, e.N, e.K, e.flags, bm, bn) * e.ksplit;
       ph.shape = shape;
       ph.mode = b.form[i] % (kDma16 + 1);
+      ph.upper |= (e.flags & G_A_UPPER) != 0;
     }
     ph.total = st.back();
     st.insert(st.end(), b.form.begin(), b.form.end());
@@ -841,10 +850,10 @@ hipError_t LaunchList::run(const void* dev, hipStream_t s) const {
     dim3 grid((unsigned)ph.total);
     if (ph.kind == PH_GEMM_F64) {
       launch_grouped<double>(reinterpret_cast<const GemmP64*>(base + ph.entries_off), st, ph.count,
-                             ph.shape, ph.mode, grid, s);
+                             ph.shape, ph.mode, ph.upper, grid, s);
     } else if (ph.kind == PH_GEMM_F32) {
       launch_grouped<float>(reinterpret_cast<const GemmP32*>(base + ph.entries_off), st, ph.count,
-                            ph.shape, ph.mode, grid, s);
+                            ph.shape, ph.mode, ph.upper, grid, s);
     } else if (ph.kind == PH_SPLIT_F64) {
       const GemmP64* e = reinterpret_cast<const GemmP64*>(base + ph.entries_off);
       grouped_split_finish<double><<<grid, 256, 0, s>>>(e, st, ph.count);

@@ -160,6 +160,7 @@ class LaunchList {
     int total;           // workgroups
     bool aligned;                   // persistent sweep
     int shape = 0, mode = 0;        // grouped products: tile shape and GemmMode (of 128 x 128)
+    bool upper = false;             // ... and whether one has G_A_UPPER
     unsigned* counters = nullptr;   // persistent: counters, queue head, error word
     int ncounters = 0;
     int ntasks = 0;

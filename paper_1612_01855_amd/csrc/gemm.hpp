@@ -1123,7 +1123,7 @@ __global__ __launch_bounds__(256) void gemm_splitk_finish(GemmParams<TIn, TCin, 
 // grid.  Entry e owns workgroups [tile_start[e], tile_start[e+1]); within an
 // entry the workgroups cover ksplit x tiles (K slice, then tile).
 template <typename TIn, typename TCin, typename TCout, typename TC2,
-          int BM, int BN, int WGM, int WGN, bool BKMAJOR, int MODE>
+          int BM, int BN, int WGM, int WGN, bool BKMAJOR, int MODE, int DIR = kByFlags>
 __global__ __launch_bounds__(WGM * WGN * 64, 2)
 void gemm_grouped_kernel(const GemmParams<TIn, TCin, TCout, TC2>* __restrict__ entries,
                          const int* __restrict__ tile_start, int nentries) {
@@ -1138,8 +1138,8 @@ void gemm_grouped_kernel(const GemmParams<TIn, TCin, TCout, TC2>* __restrict__ e
   const int tiles = gemm_wgs(p.M, p.N, p.K, p.flags, BM, BN);
   const int local = b - tile_start[lo];
   __shared__ __attribute__((aligned(1024))) char smem[tile_lds<TIn, BM, BN, BKMAJOR, MODE>()];
-  gemm_tile<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, MODE>(p, 0, local / tiles,
-                                                                   local % tiles, tiles, smem);
+  gemm_tile<TIn, TCin, TCout, TC2, BM, BN, WGM, WGN, BKMAJOR, MODE, false, DIR>(
+      p, 0, local / tiles, local % tiles, tiles, smem);
 }
 
 // How a product's operands reach LDS.  Binary64/binary32: kDma16 if the rows of both
