@@ -88,9 +88,10 @@ struct Carry {
 // not positive (or NaN) records its global row in *bad (the smallest one wins) and is
 // replaced by 1 so that the arithmetic goes on.
 //
-// Bound by the chain of columns.  128 rows take 55 us, where two leaves of 64 (one
-// wave for 64 columns one after the other, one for the inverse a step behind: 28 us,
-// 49 beside the trailing products) and the four products between them took 95.
+// Bound by the chain of columns.  64 rows take 22.5 us alone (one wave for 64 columns
+// one after the other, one for the inverse a step behind: 27.4, 49 beside the trailing
+// products); 128 rows 50 us, 55 beside them, where two such leaves and the four
+// products between them took 95.
 template <int NT>
 constexpr int kCholThreads = NT <= 4 ? 256 : 1024;
 
@@ -196,11 +197,12 @@ __global__ void chol_init_kernel(double* __restrict__ V, int64_t n, int64_t nb, 
 // replaced by 1 in the divisions of L.
 //
 // Four waves, 37 KB: the size of one workgroup of the trailing products, whose place
-// it takes when it runs beside them.  Bound by the chain of columns: 37 us (four
-// waves exchanging 64 columns one after the other through LDS: 57).  Beside the
-// trailing products it takes up to 130 us, as their matrix instructions use the same
-// binary64 units; more LDS, to keep their workgroups off the compute unit, made it
-// wait longer for its place than it gained (8192 rows: 15.4 ms; 96 or 129 KB 16.5).
+// it takes when it runs beside them.  Bound by the chain of columns: 36.5 us alone (four
+// waves exchanging 64 columns one after the other through LDS: 35, but 8 % more for the
+// factorization of 8192 rows).  Beside the trailing products of 8192 rows it takes 67 us
+// on average and up to 130, as their matrix instructions use the same binary64 units;
+// more LDS, to keep their workgroups off the compute unit, made it wait longer for its
+// place than it gained (15.4 ms then; 96 or 129 KB 16.5).
 constexpr int kLuTiles = kLeaf / 16;
 
 __global__ __launch_bounds__(256, 4) void lu_leaf_kernel(double* __restrict__ D, int64_t ldd, int s,

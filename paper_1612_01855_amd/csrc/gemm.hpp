@@ -1196,8 +1196,10 @@ inline int gemm_ksplit(const P& p, int64_t wgs, int batch, int target) {
 // direct / 64 x 64 (best of split and not), binary64: 128^3 triangular 3.7 /
 // 12.9 us, 512^3 triangular 10.7 / 19.8, 1024 x 128 x 1024 triangular 12.0 /
 // 18.9, 3968 x 128 x 128 9.5 / 10.1, 2048 x 128 x 1024 26.5 / 24.8, 1024 x 1024 x
-// 128 15.6 / 11.0.  C may be neither A nor B: another workgroup would read
-// what one has overwritten.
+// 128 15.6 / 11.0.  With one wave a tile (more than 2048 tiles: launch_direct) the rate
+// is half of that, so that near the line the 64 x 64 tiles would be ahead: three 512^3
+// triangular products, right on it, take 38 us.  C may be neither A nor B: another
+// workgroup would read what one has overwritten.
 template <typename TIn, typename P>
 inline bool direct_ok(const P& p, int batch) {
   if ((const void*)p.Cout == (const void*)p.A || (const void*)p.Cout == (const void*)p.B)

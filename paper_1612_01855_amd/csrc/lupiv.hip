@@ -152,8 +152,8 @@ __device__ __forceinline__ int best_lane(const Cand& c) {
 // statically (4 and 2 measured the same to 4 % slower); after a group the
 // columns move down by kSub places (cyclically: after kPw / kSub groups they
 // are back), and columns that already hold L are left out of the update.
-// Measured per column: about 1.1 us on one workgroup, 2.4 us on several (1.3
-// of it the store and load of the candidates); 11 to 16 us with one
+// Measured per column: 1.3 us on one workgroup (1.75 with two rows a thread), 2.45 us
+// on several (1.3 of it the store and load of the candidates); 11 to 16 us with one
 // device-wide arrival counter and fences a column and 256 rows a workgroup.
 template <int RPT, bool MULTI>
 __global__ __launch_bounds__(kThreads) void piv_panel_kernel(
@@ -596,8 +596,8 @@ hipError_t prod(const double* A, int64_t lda, const double* B, int64_t ldb, doub
 // one row per thread are launched like any other kernel where the device has room
 // for many such panels (plain_groups): every kernel beside them ends by itself, and a
 // wait that lasts all the same ends at kSpinLimit with the error word set.  A
-// cooperative launch idles about 11 us before and after it (n = 4096, 96 panels of 82
-// us: 15.7 ms with it, 13.8 without) and remains for more workgroups and for smaller
+// cooperative launch idles about 11 us before and after it (n = 4096, 96 panels of 78
+// us: 15.7 ms with it, 13.7 without) and remains for more workgroups and for smaller
 // devices.
 
 // Panels' workgroups of one row per thread that the current device has room for;
